@@ -1,5 +1,5 @@
-// bf16 GEMM on gfx950 MFMA (v_mfma_f32_32x32x16_bf16) with the fused
-// epilogues of the DiT blocks:  C = epi(A . W^T + bias).
+// bf16 GEMM on gfx950 MFMA with the fused epilogues of the DiT blocks:
+// C = epi(A . W^T + bias).
 //
 // A [M,K] and W [N,K] are both K-contiguous (W in nn.Linear [out,in]
 // layout), so every MFMA operand is a 16-byte run of K.  Tiles are staged
@@ -7,9 +7,10 @@
 // destination, the 16-byte chunks of each row XOR-swizzled by
 // ((row >> 1) & 7): two consecutive 128-byte rows fill one 256-byte bank
 // cycle, so the fragment reads of 16 consecutive rows hit 16 distinct 16-byte
-// bank groups.  The main kernel (256 x 256 tiles, 8 waves of 64 x 128) keeps
-// a ring of five operand slices in LDS: W slices (cold, from HBM) arrive two
-// slices ahead of use, A slices one; smaller tiles use a two-stage pipeline.
+// bank groups.  The main kernel (256 x 256 tiles, 8 waves of 64 x 128,
+// 16x16x32 MFMAs) keeps a ring of five operand slices in LDS: W slices (cold,
+// from HBM) arrive two slices ahead of use, A slices one; smaller tiles use a
+// two-stage pipeline on 32x32x16 MFMAs.
 // Workgroups are remapped so that each of the 8 XCDs walks a contiguous,
 // M-grouped range of tiles (its own L2 sees the shared A rows / W columns).
 #include <type_traits>
@@ -305,11 +306,34 @@ struct EpiLds {
         const int c = (j * 32 + lrow) ^ (((row >> 2) & 1) << 5);
         slab[row * 128 + c] = a[j][r];
       }
+    slab_rows<1, 5>(i, old);
+  }
+
+  // The same for 16 x 16 blocks (a: rows 0..15, b: rows 16..31): lane (lr, lq)
+  // holds column lr and rows 4 lq .. 4 lq + 3 of each; columns XOR 16 ((row >> 2) & 3)
+  // send the four lane quarters of a write to different banks.
+  __device__ __forceinline__ void slab_pass16(const f32x4_t (&a)[8], const f32x4_t (&b)[8], int i,
+                                              const uint2 (&old)[8][2], int lr, int lq) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = (16 * j + lr) ^ (lq << 4);
+        slab[(4 * lq + r) * 128 + c] = a[j][r];
+        slab[(16 + 4 * lq + r) * 128 + c] = b[j][r];
+      }
+    slab_rows<3, 4>(i, old);
+  }
+
+  // Reads the staged slab back as 8-column row segments (columns XOR
+  // ((row >> 2) & MASK) << SH), applies the epilogue and stores.
+  template <int MASK, int SH>
+  __device__ __forceinline__ void slab_rows(int i, const uint2 (&old)[8][2]) {
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0) only
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
       const int row = rq + 4 * p;
-      const int sw = ((row >> 2) & 1) << 5;
+      const int sw = ((row >> 2) & MASK) << SH;
       float v[2][4];
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
@@ -634,50 +658,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(Batch b) 
   }
 }
 
-// Transposed values straight from the accumulators of a wave that owns 64
-// rows x one 128-column head group (TM = 2, TN = 4).  In a 32 x 32 block,
-// lane (lrow, lhalf) holds column lrow and rows 8 (r / 4) + 4 lhalf + r % 4;
-// with the key order of the transposed layout (slot 8 ((k >> 2) & 1) +
-// 4 (k >> 3) + (k & 3) inside each 16-key group) its registers r = 0..7 are
-// slots 8 lhalf .. 8 lhalf + 7 of the first group and r = 8..15 the same
-// slots of the second, so each lane stores two 16-byte runs per block.  The
-// host admits this only for 32-row aligned segments (a block is one
-// sequence's keys kb .. kb + 31, kb a multiple of 32), or for one sequence in
-// one piece, whose last block may end past its last key inside the padded
-// key range).
-__device__ __forceinline__ void store_vt(const Prob& P, const f32x16_t (&acc)[2][4], int m_base, int ncol0,
-                                         int lrow, int lhalf) {
-  const int h = (ncol0 - P.vt_col0) >> 7;
-  float bias[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) bias[j] = P.bias ? bf16_to_f32(P.bias[ncol0 + 32 * j + lrow]) : 0.f;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int m = m_base + 32 * i;
-    if (m >= P.M) continue;
-    int z, key;
-    if (m < P.vt_split) {
-      z = m / P.vt_rows0;
-      key = P.vt_key0 + m % P.vt_rows0;
-    } else {
-      const int mm = m - P.vt_split;
-      z = mm / P.vt_rows1;
-      key = P.vt_key1 + mm % P.vt_rows1;
-    }
-    bf16_t* base = P.vt + ((int64_t)(z * P.vt_heads + h) * 128 + lrow) * P.vt_ld + key + 8 * lhalf;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const f32x16_t& a = acc[i][j];
-      const float b = bias[j];
-      bf16_t* row = base + (int64_t)(32 * j) * P.vt_ld;
-      *(uint4*)row = make_uint4(pack_bf16x2(a[0] + b, a[1] + b), pack_bf16x2(a[2] + b, a[3] + b),
-                                pack_bf16x2(a[4] + b, a[5] + b), pack_bf16x2(a[6] + b, a[7] + b));
-      *(uint4*)(row + 16) = make_uint4(pack_bf16x2(a[8] + b, a[9] + b), pack_bf16x2(a[10] + b, a[11] + b),
-                                       pack_bf16x2(a[12] + b, a[13] + b), pack_bf16x2(a[14] + b, a[15] + b));
-    }
-  }
-}
-
 // vmcnt(N) and lgkmcnt(0) in one wait (same encoding as wait_vmcnt).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt_lgkm0() {
@@ -692,22 +672,72 @@ __device__ __forceinline__ void wait_vmcnt_lgkm0() {
 // it; callers wait for their own LDS reads and copies first.
 __device__ __forceinline__ void barrier_no_fence() { asm volatile("s_barrier" ::: "memory"); }
 
+// Transposed values straight from the accumulators of a wave that owns 64
+// rows x one 128-column head group (4 x 8 blocks of 16 x 16).  In a block,
+// lane (lr, lq) holds column lr and rows 4 lq .. 4 lq + 3; with the key order
+// of the transposed layout (slot 8 ((k >> 2) & 1) + 4 (k >> 3) + (k & 3)
+// inside each 16-key group) these are the four consecutive slots from
+// 8 (lq & 1) + 4 (lq >> 1), one 8-byte store.  The host admits this only for
+// 32-row aligned segments (a pair of blocks is one sequence's keys kb ..
+// kb + 31, kb a multiple of 32), or for one sequence in one piece, whose last
+// pair may end past its last key inside the padded key range.
+__device__ __forceinline__ void store_vt(const Prob& P, const f32x4_t (&acc)[4][8], int m_base, int ncol0,
+                                           int lr, int lq) {
+  const int h = (ncol0 - P.vt_col0) >> 7;
+  float bias[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) bias[j] = P.bias ? bf16_to_f32(P.bias[ncol0 + 16 * j + lr]) : 0.f;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int m = m_base + 32 * i;
+    if (m >= P.M) continue;
+    int z, key;
+    if (m < P.vt_split) {
+      z = m / P.vt_rows0;
+      key = P.vt_key0 + m % P.vt_rows0;
+    } else {
+      const int mm = m - P.vt_split;
+      z = mm / P.vt_rows1;
+      key = P.vt_key1 + mm % P.vt_rows1;
+    }
+    bf16_t* base = P.vt + ((int64_t)(z * P.vt_heads + h) * 128 + lr) * P.vt_ld + key + 8 * (lq & 1) + 4 * (lq >> 1);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const f32x4_t& a = acc[2 * i + e][j];
+        const float b = bias[j];
+        *(uint2*)(base + (int64_t)(16 * j) * P.vt_ld + 16 * e) =
+            make_uint2(pack_bf16x2(a[0] + b, a[1] + b), pack_bf16x2(a[2] + b, a[3] + b));
+      }
+  }
+}
 // 256 x 256 tiles, 8 waves of 64 x 128, BK = 64, with the whole 160 KB of
 // LDS as a ring of five 32 KB operand slices: operand i (W slice s = 2s,
-// A slice s = 2s + 1) lives in unit i % 5.  When slice kt starts, the units
-// of slice kt-1 are free and receive A slice kt+1 and W slice kt+2, so W
-// slices are copied two slices ahead of use and A slices one ahead, and the
-// end-of-slice wait leaves the W copies in flight.  The weights lead: they
-// come cold from HBM, while A was mostly written just before (about 3%
-// faster over the block-stack shapes than A leading; same result bits).
-// The substep schedule is the one of the two-stage kernel above (fragments
-// double-buffered in registers, LDS reads of the next substep between the
-// MFMAs).
+// A slice s = 2s + 1) lives in unit i % 5.  W slices are copied two slices
+// ahead of use and A slices one ahead: the weights come cold from HBM, while
+// A was mostly written just before.
+//
+// What bounds it is the board's power: under these launches the clock sits at
+// 1.7-1.9 GHz and falls as the MFMAs get busier, so energy per product counts,
+// not issue slots.  16x16x32 MFMAs read and write each accumulator once per
+// 32 of K (32x32x16: once per 16) for the same fragment reads from LDS, and
+// give the same bits.  Measured against 32x32x16 in turn on one card, through
+// the entry point: 4608 x 9216 x 3072 with the RMS norm 247.5 -> 232.0 us,
+// 4608 x 12288 x 3072 GELU 329.6 -> 307.5, 4608 x 3072 x 12288 gated 289.4 ->
+// 274.7, 8192^3 plain 1356 -> 1413 TFLOP/s, 32760 x 13824 x 5120 GELU 3566 ->
+// 3432 us.  With 32x32x16, four waves of 128 x 128 (two thirds of the LDS
+// reads) ran at 0.99 of the eight waves' rate in the main loop and at 0.92-0.96
+// over the K = 3072 layers, whose epilogue then has one wave per SIMD.
+//
+// A 32-deep substep reads its 12 fragments under the first 24 of the previous
+// substep's 32 MFMAs (W fragment j is dead after its four MFMAs, so about 16
+// fragments are live); a scheduling fence closes each substep.
 // Requires K % 64 == 0, K >= 128 and the LDS-staged epilogue's conditions.
 template <int KIND>
 __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(Batch b) {
   constexpr int BM = 256, BN = 256, BK_ = 64, WGN = 2;
-  constexpr int WM = 64, WN = 128, TM = 2, TN = 4;
+  constexpr int WM = 64, WN = 128, TM = 4, TN = 8;
   constexpr int UNIT = 256 * BK_ * 2;  // one operand slice
   constexpr int INS = 4;                // 1 KB copies per wave per operand slice
   __shared__ __attribute__((aligned(1024))) char smem[5 * UNIT];
@@ -732,7 +762,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(Batch b) {
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  const int lrow = lane & 31, lhalf = lane >> 5;
+  const int lr = lane & 15, lq = lane >> 4;
 
   // per-lane source byte offsets: copy j of this wave moves rows
   // 8 (4 wave + j) .. + 7 of the slice, 16-byte chunks XOR-swizzled by
@@ -745,112 +775,104 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(Batch b) {
     aoff[j] = ((uint32_t)min(m0 + row, P.M - 1) * (uint32_t)P.lda + c * 8) * 2u;
     boff[j] = ((uint32_t)min(n0 + row, P.N - 1) * (uint32_t)P.ldw + c * 8) * 2u;
   }
-  auto unit = [&](int op) { return smem + (op % 5) * UNIT; };
-  auto issue_a = [&](int s) {
-    char* d = unit(2 * s + 1);
+  auto issue = [&](const bf16_t* base, const uint32_t (&off)[INS], int u, int s) {
+    char* d = smem + u;
     const uint32_t so = (uint32_t)s * BK_ * 2;
 #pragma unroll
-    for (int j = 0; j < INS; ++j) buf_lds16(P.A, (lds_void_t*)(d + (wave * INS + j) * 1024), aoff[j], so);
+    for (int j = 0; j < INS; ++j) buf_lds16(base, (lds_void_t*)(d + (wave * INS + j) * 1024), off[j], so);
   };
-  auto issue_w = [&](int s) {
-    char* d = unit(2 * s);
-    const uint32_t so = (uint32_t)s * BK_ * 2;
+  // this lane's fragment offset inside 16 rows of a unit: row lr, k = 32 s + 8 lq .. + 7
+  int loff[2];
 #pragma unroll
-    for (int j = 0; j < INS; ++j) buf_lds16(P.W, (lds_void_t*)(d + (wave * INS + j) * 1024), boff[j], so);
+  for (int s = 0; s < 2; ++s) loff[s] = lr * 128 + (((4 * s + lq) ^ ((lr >> 1) & 7)) << 4);
+  auto rd = [&](int uw, int ua, int s, bf16x8_t(&af)[TM], bf16x8_t(&bfr)[TN]) {
+    const char* sA = smem + ua + wm * WM * 128 + loff[s];
+    const char* sB = smem + uw + wn * WN * 128 + loff[s];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) af[i] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sA + i * 16 * 128));
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bfr[j] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sB + j * 16 * 128));
   };
-  auto rd = [&](int kt, int s, bf16x8_t(&af)[TM], bf16x8_t(&bfr)[TN]) {
-    const char* sA = unit(2 * kt + 1);
-    const char* sB = unit(2 * kt);
-    const int kc = 2 * s + lhalf;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int row = wm * WM + i * 32 + lrow;
-      af[i] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sA + row * 128 + ((kc ^ ((row >> 1) & 7)) << 4)));
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int row = wn * WN + j * 32 + lrow;
-      bfr[j] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sB + row * 128 + ((kc ^ ((row >> 1) & 7)) << 4)));
-    }
-  };
-  f32x16_t acc[TM][TN];
+  f32x4_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  EpiLds<KIND> epi(P, m0 + wm * WM, n0 + wn * WN, lrow, lhalf, (float*)smem + wave * (32 * 128));
-  epi.prep();
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // bias and column map are loaded before the K loop; the gated epilogue's
+  // gate values beside them would spill, and its own loads of the old rows
+  // wait after the loop in any case
+  EpiLds<KIND> epi(P, m0 + wm * WM, n0 + wn * WN, lane & 31, lane >> 5, (float*)smem + wave * (32 * 128));
+  if constexpr (KIND == EPI_K_STORE) epi.prep();
   auto mm = [&](const bf16x8_t(&af)[TM], const bf16x8_t(&bfr)[TN]) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+      for (int i = 0; i < TM; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
   };
-  // one MFMA, then the copies of this substep (if any) and two LDS reads,
-  // three times; then the other five MFMAs; a fence closes the substep
+  // per MFMA: a fragment read of the next substep after every second one, and
+  // the four copies of this substep (if any) spread between them
   auto sched = [&](auto with_copy) {
     constexpr bool WithCopy = decltype(with_copy)::value;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
+    for (int q = 0; q < 32; ++q) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-      if constexpr (WithCopy) __builtin_amdgcn_sched_group_barrier(0x010, 2, 0);  // VMEM
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // DS read
+      if (q % 2 == 1 && q < 24) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
+      if (WithCopy && q % 6 == 2 && q < 24) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);  // VMEM
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - 3, 0);
     __builtin_amdgcn_sched_barrier(0);
-  };
-  using copy_t = std::integral_constant<bool, true>;
-  using nocopy_t = std::integral_constant<bool, false>;
-
-  const int nk = P.K / BK_;  // >= 2
-  bf16x8_t a0[TM], b0[TN], a1[TM], b1[TN];
-  issue_w(0);
-  issue_a(0);
-  issue_w(1);
-  wait_vmcnt_lgkm0<INS>();  // slice 0 has landed; W slice 1 may be in flight
-  barrier_no_fence();
-  rd(0, 0, a0, b0);
-  // slice kt with A slice kt+1 (H1) and W slice kt+2 (H2) copied meanwhile
-  auto slice = [&](int kt, auto h1, auto h2) {
-    constexpr bool H1 = decltype(h1)::value, H2 = decltype(h2)::value;
-    if constexpr (H1) issue_a(kt + 1);
-    rd(kt, 1, a1, b1); mm(a0, b0);
-    if constexpr (H1) sched(copy_t{}); else sched(nocopy_t{});
-    if constexpr (H2) issue_w(kt + 2);
-    rd(kt, 2, a0, b0); mm(a1, b1);
-    if constexpr (H2) sched(copy_t{}); else sched(nocopy_t{});
-    rd(kt, 3, a1, b1); mm(a0, b0); sched(nocopy_t{});
-    mm(a1, b1);
-    // slice kt+1 has landed (W slice kt+2 may still be in flight) and every
-    // LDS read of slice kt has returned, so after the barrier its units are free
-    if constexpr (H2) wait_vmcnt_lgkm0<INS>();
-    else __builtin_amdgcn_s_waitcnt(0);
-    barrier_no_fence();
   };
   using yes = std::integral_constant<bool, true>;
   using no = std::integral_constant<bool, false>;
-  for (int kt = 0; kt < nk - 2; ++kt) {
-    slice(kt, yes{}, yes{});
-    rd(kt + 1, 0, a0, b0);
-  }
-  slice(nk - 2, yes{}, no{});
-  rd(nk - 1, 0, a0, b0);
-  rd(nk - 1, 1, a1, b1); mm(a0, b0); sched(nocopy_t{});
-  rd(nk - 1, 2, a0, b0); mm(a1, b1); sched(nocopy_t{});
-  rd(nk - 1, 3, a1, b1); mm(a0, b0); sched(nocopy_t{});
+
+  const int nk = P.K / BK_;  // >= 2
+  bf16x8_t a0[TM], b0[TN], a1[TM], b1[TN];
+  // unit offsets of W kt, A kt, W kt+1, A kt+1, W kt+2
+  int u0 = 0, u1 = UNIT, u2 = 2 * UNIT, u3 = 3 * UNIT, u4 = 4 * UNIT;
+  issue(P.W, boff, u0, 0);
+  issue(P.A, aoff, u1, 0);
+  issue(P.W, boff, u2, 1);
+  issue(P.A, aoff, u3, 1);
+  wait_vmcnt_lgkm0<2 * INS>();  // slice 0 has landed; slice 1 may be in flight
+  barrier_no_fence();
+  rd(u0, u1, 0, a0, b0);
+  // Slice kt.  Its last fragments are in registers after the first substep:
+  // there the wave waits for its own copies of slice kt+1 (W slice kt+2 may
+  // stay in flight) and meets the others, so that the units of slice kt are
+  // free for A slice kt+2 and (a substep later) W slice kt+3, and the first
+  // fragments of slice kt+1 are read under the MFMAs of the second substep.
+  // MORE: slice kt+2 exists.
+  auto slice = [&](int kt, auto more) {
+    constexpr bool MORE = decltype(more)::value;
+    if constexpr (MORE) issue(P.W, boff, u4, kt + 2);
+    rd(u0, u1, 1, a1, b1); mm(a0, b0);
+    if constexpr (MORE) sched(yes{}); else sched(no{});
+    if constexpr (MORE) wait_vmcnt_lgkm0<INS>();
+    else __builtin_amdgcn_s_waitcnt(0);
+    barrier_no_fence();
+    if constexpr (MORE) issue(P.A, aoff, u0, kt + 2);
+    rd(u2, u3, 0, a0, b0); mm(a1, b1);
+    if constexpr (MORE) sched(yes{}); else sched(no{});
+    const int t0 = u0, t1 = u1;
+    u0 = u2; u1 = u3; u2 = u4; u3 = t0; u4 = t1;
+  };
+  for (int kt = 0; kt < nk - 2; ++kt) slice(kt, yes{});
+  slice(nk - 2, no{});
+  rd(u0, u1, 1, a1, b1); mm(a0, b0); sched(no{});
   mm(a1, b1);
   __syncthreads();  // every wave is done with the ring before the epilogue reuses LDS
   if constexpr (KIND == EPI_K_STORE) {
     const int ncol0 = n0 + wn * WN;  // wave-uniform: whole head groups are values or not
     if (P.vt && ncol0 >= P.vt_col0 && ncol0 < P.vt_col0 + 128 * P.vt_heads) {
-      store_vt(P, acc, m0 + wm * WM, ncol0, lrow, lhalf);
+      store_vt(P, acc, m0 + wm * WM, ncol0, lr, lq);
       return;
     }
   }
-  epilogue_lds_impl<TM>(epi, acc, std::make_index_sequence<TM>{});
+  if constexpr (KIND != EPI_K_STORE) epi.prep();
+  uint2 old[2][8][2];
+  if (epi.gated) { epi.load_old(0, old[0]); epi.load_old(1, old[1]); }
+  epi.slab_pass16(acc[0], acc[1], 0, old[0], lr, lq);
+  epi.slab_pass16(acc[2], acc[3], 1, old[1], lr, lq);
 }
 
 typedef __bf16 bf16x8v_t __attribute__((ext_vector_type(8)));

@@ -118,6 +118,33 @@ def test_gemm_ring_pipeline_ragged(gated):
         assert_bf16_close(host_bf16(cbuf), round_bf16(c0 + g.astype(np.float64) * y))
 
 
+@pytest.mark.parametrize("K", [128, 192])
+@pytest.mark.parametrize("flags", [binding.EPI_STORE, binding.EPI_F32, binding.EPI_GATED_RES])
+def test_gemm_ring_shortest_pipelines(K, flags):
+    """The ring kernel at its two and three slices of K (prologue and peeled
+    tail only; one steady slice), one ragged row of 256 x 256 tiles that fills
+    the chip once, with each of its three epilogues."""
+    torch = torch_cuda()
+    M, N = 250, 65528
+    a_b, a = make((M, K))
+    w_b, w = make((N, K), 0.05)
+    b_b, b = make((N,), 0.1)
+    y = a @ w.T + b
+    args = dict(M=M, N=N, K=K, flags=flags)
+    if flags == binding.EPI_F32:
+        out = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+        binding.gemm_bf16(dev(torch, a_b), dev(torch, w_b), dev(torch, b_b), out, **args)
+        np.testing.assert_allclose(out.cpu().numpy(), y, rtol=1e-5, atol=1e-5)
+        return
+    c0_b, c0 = make((M, N))
+    g = RNG.standard_normal(N).astype(np.float32)
+    gated = flags == binding.EPI_GATED_RES
+    out = dev(torch, c0_b)
+    binding.gemm_bf16(dev(torch, a_b), dev(torch, w_b), dev(torch, b_b), out, gate=dev(torch, g) if gated else None,
+                      **args)
+    assert_bf16_close(host_bf16(out), round_bf16(c0 + g.astype(np.float64) * y if gated else y))
+
+
 def test_gemm_ring_rms_gelu_gap_ragged():
     """The ring kernel's store epilogue with the single-block projection's
     column roles at a ragged M: per-head RMS on the first 2 H columns, GELU
