@@ -291,7 +291,7 @@ def main():
     # dominant kernel class: the MFMA class with the most event time
     dom = "attn" if ms["attn"] > ms["gemm"] else "gemm"
     dom_kernel = {"gemm": ("gemm_bf16_ring_kernel", "bf16 GEMM (block-stack linear layers)", "gemm_bf16.hip"),
-                  "attn": ("flash_attn_pipe_kernel", "bf16 flash attention (self- and cross-attention)",
+                  "attn": ("flash_attn_kernel", "bf16 flash attention (self- and cross-attention)",
                            "attention.hip")}[dom]
     launches = max(st["launches"][dom], 1)
     dom_tflops = work[dom] / (ms[dom] * 1e-3) / 1e12 if ms[dom] else 0.0

@@ -72,7 +72,11 @@ enum {
  * ldq), k and v [Lk, heads*128] (ldk, ldv), o [Lq, heads*128] (ldo);
  * head h occupies columns [128h, 128h + 128).  flags: 0 or
  * DIT_ATTN_BOUNDED_LOGITS.  vt_ws is a device workspace of heads * 128 *
- * round_up(Lk, 64) bf16 elements that receives v transposed per head.
+ * round_up(Lk, 64) bf16 elements that receives v transposed per head.  Where
+ * the work fills the chip's CUs only partly in its last round, the key ranges
+ * are shared out and the parts added from f32 sums in device memory of the
+ * library; with more than two such calls in flight on one GPU the further ones
+ * run unshared (the same result up to the rounding of f32 sums).
  * Errors: DIT_EINVAL, DIT_ESHAPE (Lq, Lk < 1), DIT_EHIP. */
 dit_status dit_attention_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk,
                               const void* v, int64_t ldv, void* o, int64_t ldo,

@@ -1,26 +1,22 @@
 // Attention kernels of the DiT blocks.
 //
-// bf16 flash attention (head_dim 128) on gfx950 MFMA 32x32x16.  The score
-// tile is computed transposed, S^T = K Q^T, so each lane owns one query
-// column and its softmax statistics: the row max needs one exchange with the
-// partner lane (lane ^ 32) and the running rescale of the output is a
-// per-lane scalar.  The output is accumulated transposed as well,
-// O^T = V^T P^T, which lets the probabilities feed the second MFMA straight
-// from the score accumulators (same lane, same registers); V is therefore
-// read from a per-head transposed copy [128][keys] whose keys are permuted
-// inside 16-key groups so each operand is one 16-byte LDS read.  K and V^T
-// tiles of 64 keys are DMA'd into XOR-swizzled LDS, three tiles resident.
+// bf16 flash attention (head_dim 128) on gfx950 MFMA 16x16x32.  The score
+// tile is computed transposed, S^T = K Q^T, so each lane holds one query's
+// scores: row statistics need one exchange over the four lanes of a query and
+// the running rescale of the output is a per-lane scalar.  The output is
+// accumulated transposed as well, O^T = V^T P^T, which lets the probabilities
+// feed the second MFMA straight from the score accumulators (same lane, same
+// registers); V is therefore read from a per-head transposed copy [128][keys]
+// whose keys are permuted inside 32-key groups so each operand is one 16-byte
+// LDS read.  K and V^T tiles of 64 keys are copied into XOR-swizzled LDS.
 // With bounded logits (unit-gain RMS-normalised q and k) a fixed shift
 // replaces the running max; the row sum takes the bf16-rounded P with a
 // packed dot product.  Exact-softmax semantics (non-causal), f32 statistics,
-// output normalised once at the end.  The sampler's bounded-logit launches
-// use a software-pipelined form of the same arithmetic (flash_attn_pipe_kernel):
-// each iteration overlaps the softmax of one key tile (VALU) with the PV
-// product of the previous tile and the score product of the next (MFMA).
+// output normalised once at the end.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
-
 
 #include "common.h"
 #include "kernels.h"
@@ -35,9 +31,9 @@ constexpr float RESCALE_SLACK = 8.f;  // log2 units a stale max may lag behind
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) void glb_void_t;
 
-// Position of key k (0..15) inside its 16-key group of the transposed V:
-// the two 4-key runs a lane half needs for one MFMA k-step become adjacent.
-__host__ __device__ constexpr int vt_slot(int k) { return 8 * ((k >> 2) & 1) + 4 * (k >> 3) + (k & 3); }
+// Position of key k (0..31) inside its 32-key group of the transposed V: the
+// two 4-key runs a lane quarter needs for one MFMA k-step become adjacent.
+__host__ __device__ constexpr int vt_slot(int k) { return 8 * ((k >> 2) & 3) + 4 * (k >> 4) + (k & 3); }
 
 // LDS tiles (bf16, no padding): K [64 keys][128 d], 16-byte chunk c of row r
 // stored at chunk c ^ (r & 15); V^T [128 d][64 keys], chunk c of row d at
@@ -60,10 +56,9 @@ struct RowMap {
 struct SeqMap {
   int split;
   int64_t gap0, gz, zs;
-  __device__ __forceinline__ RowMap at(int z) const { return RowMap{split, gap0 + z * gz, z * zs}; }
+  __host__ __device__ __forceinline__ RowMap at(int z) const { return RowMap{split, gap0 + z * gz, z * zs}; }
 };
 
-constexpr int NSTAGE = 3;     // K / V^T tiles resident: t (V), t + 1 (K), t + 2 (in flight)
 constexpr int TILE_BYTES = 2 * KT * D * 2;
 
 // With q and k RMS-normalised to unit gain, |q.k| <= |q||k| <= 128, so a
@@ -73,477 +68,629 @@ constexpr int TILE_BYTES = 2 * KT * D * 2;
 // exp(s - 11.5) <= 1.
 constexpr float BOUNDED_SHIFT_LOG2 = 11.5f * 1.4426950408889634f;
 
-// QG 32-query groups per wave, NW waves per workgroup.
-template <bool BOUNDED, int QG, int NW>
-__global__ __launch_bounds__(64 * NW) void flash_attn_bf16_kernel(
-    const bf16_t* __restrict__ q, int64_t ldq, const bf16_t* __restrict__ k, int64_t ldk,
-    const bf16_t* __restrict__ vt, int ldvt, bf16_t* __restrict__ o, int64_t ldo, int Lq, int Lk,
-    float scale_log2, SeqMap sm) {
-  __shared__ __attribute__((aligned(1024))) char smem[NSTAGE][TILE_BYTES];  // [stage][K | V^T]
-  const RowMap rm = sm.at(blockIdx.z);
-  vt += (int64_t)blockIdx.z * gridDim.y * D * ldvt;
-
-  constexpr int QW = 32 * QG, QB = NW * QW;
-  constexpr int CPW = 16 / NW;  // 1 KB copies per wave for each of K and V^T
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lrow = lane & 31, lhalf = lane >> 5;
-  const int h = blockIdx.y;
-  const int q0 = blockIdx.x * QB + wave * QW;
-
-  // Q^T fragments (B operand): lane holds d = 16 s + 8 lhalf + [0, 8) of query q0 + 32 g + lrow.
-  bf16x8_t qf[QG][8];
-#pragma unroll
-  for (int g = 0; g < QG; ++g) {
-    const int qr = min(q0 + 32 * g + lrow, Lq - 1);
-    const bf16_t* qp = q + rm(qr) * ldq + h * D + 8 * lhalf;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) qf[g][s] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(qp + 16 * s));
-  }
-
-  const bf16_t* kh = k + h * D;
-  const bf16_t* vh = vt + (int64_t)h * D * ldvt;
-  // Direct global -> LDS copies: each instruction moves 64 x 16 bytes to a
-  // contiguous 1 KB; the lane -> (row, chunk) choice realises the swizzle.
-  auto issue_tile = [&](int t) {
-    const int kb0 = t * KT;
-    char* sk = smem[t % NSTAGE];
-    char* sv = sk + KT * D * 2;
-#pragma unroll
-    for (int j = 0; j < CPW; ++j) {
-      const int ii = wave * CPW + j;
-      {  // K rows 4 ii .. 4 ii + 3
-        const int row = 4 * ii + (lane >> 4);
-        const int c = (lane & 15) ^ (row & 15);
-        const int key = min(kb0 + row, Lk - 1);
-        __builtin_amdgcn_global_load_lds((glb_void_t*)(kh + rm(key) * ldk + c * 8),
-                                         (lds_void_t*)(sk + ii * 1024), 16, 0, 0);
-      }
-      {  // V^T rows 8 ii .. 8 ii + 7
-        const int d = 8 * ii + (lane >> 3);
-        const int c = (lane & 7) ^ ((d >> 1) & 7);
-        __builtin_amdgcn_global_load_lds((glb_void_t*)(vh + (int64_t)d * ldvt + kb0 + c * 8),
-                                         (lds_void_t*)(sv + ii * 1024), 16, 0, 0);
-      }
-    }
-  };
-
-  // S^T = K Q^T for the 64 keys of tile t (32 MFMAs)
-  auto scores = [&](int t, f32x16_t (&sacc)[QG][2]) {
-    const char* sk = smem[t % NSTAGE];
-#pragma unroll
-    for (int g = 0; g < QG; ++g)
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[g][kb][r] = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sk + k_off(kb * 32 + lrow, 2 * s + lhalf)));
-#pragma unroll
-        for (int g = 0; g < QG; ++g)
-          sacc[g][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[g][s], sacc[g][kb], 0, 0, 0);
-      }
-  };
-
-  f32x16_t oacc[QG][4];
-#pragma unroll
-  for (int g = 0; g < QG; ++g)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[g][i][r] = 0.f;
-  float m_run[QG], l_run[QG];
-#pragma unroll
-  for (int g = 0; g < QG; ++g) {
-    m_run[g] = BOUNDED ? BOUNDED_SHIFT_LOG2 : -INFINITY;
-    l_run[g] = 0.f;
-  }
-
-  // softmax of tile t (VALU) and O^T += V^T P^T (32 MFMAs)
-  auto softmax_pv = [&](int t, f32x16_t (&sacc)[QG][2]) {
-    const int kbase = t * KT;
-    const bool ragged = kbase + KT > Lk;
-    bf16x8_t pf[QG][4];
-#pragma unroll
-    for (int g = 0; g < QG; ++g) {
-      if (ragged) {
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = kbase + kb * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3);
-            if (key >= Lk) sacc[g][kb][r] = -INFINITY;
-          }
-      }
-      if constexpr (!BOUNDED) {
-        float mx = -INFINITY;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[g][kb][r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2;
-        // Keep a stale running max unless the new one is more than
-        // RESCALE_SLACK above it (exact: softmax is shift invariant).
-        const bool need = mx > m_run[g] + RESCALE_SLACK;
-        if (__builtin_amdgcn_ballot_w64(need)) {
-          const float m_new = need ? mx : m_run[g];
-          const float alpha = __builtin_amdgcn_exp2f(m_run[g] - m_new);
-          l_run[g] *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[g][dt][r] *= alpha;
-          m_run[g] = m_new;
-        }
-      }
-      const float mneg = -m_run[g];
-      float ls = 0.f;
-      const bf16x2_t ones = {(__bf16)1.f, (__bf16)1.f};
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        uint32_t w[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[g][kb][2 * j], scale_log2, mneg));
-          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[g][kb][2 * j + 1], scale_log2, mneg));
-          w[j] = pack_bf16x2(p0, p1);
-          // the row sum takes exactly the rounded P the second product uses
-          ls = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w[j]), ones, ls, false);
-        }
-        pf[g][2 * kb] = __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
-        pf[g][2 * kb + 1] = __builtin_bit_cast(bf16x8_t, make_uint4(w[4], w[5], w[6], w[7]));
-      }
-      l_run[g] += ls;
-    }
-    const char* sv = smem[t % NSTAGE] + KT * D * 2;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const bf16x8_t vf =
-            __builtin_bit_cast(bf16x8_t, *(const uint4*)(sv + v_off(dt * 32 + lrow, 2 * ks + lhalf)));
-#pragma unroll
-        for (int g = 0; g < QG; ++g)
-          oacc[g][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[g][ks], oacc[g][dt], 0, 0, 0);
-      }
-  };
-
-  const int ntiles = (Lk + KT - 1) / KT;
-  issue_tile(0);
-  if (ntiles > 1) issue_tile(1);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-
-  f32x16_t sc[QG][2];
-  for (int t = 0; t < ntiles; ++t) {
-    if (t + 2 < ntiles) issue_tile(t + 2);  // overwrites tile t - 1, finished before the last barrier
-    scores(t, sc);
-    softmax_pv(t, sc);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-  }
-
-#pragma unroll
-  for (int g = 0; g < QG; ++g) {
-    const int qi = q0 + 32 * g + lrow;
-    const float l = l_run[g] + __shfl_xor(l_run[g], 32, 64);
-    const float inv = 1.f / l;
-    if (qi < Lq) {
-      bf16_t* op = o + rm(qi) * ldo + h * D;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int d0 = dt * 32 + 8 * r4 + 4 * lhalf;
-          *(uint2*)(op + d0) = make_uint2(pack_bf16x2(oacc[g][dt][4 * r4] * inv, oacc[g][dt][4 * r4 + 1] * inv),
-                                          pack_bf16x2(oacc[g][dt][4 * r4 + 2] * inv, oacc[g][dt][4 * r4 + 3] * inv));
-        }
-    }
-  }
-}
-
-// Software-pipelined variant (bounded logits only): iteration t runs the
-// PV product of tile t-1 and the score product of tile t+1 (MFMA) together
-// with the softmax of tile t (VALU), which depends on neither.  Five LDS
-// stages: tiles t-1 (V), t, t+1 (K), t+2 and t+3 (in flight).  The loop is
-// unrolled by two so the score and probability buffers alternate statically
-// (no register copies), each lane's fragment offsets inside a stage are
-// computed once (one add of the stage base per offset and tile), and in the
-// steady state a tile's copies take one uniform base plus fixed per-lane
-// byte offsets.  Each steady iteration is scheduled explicitly: three LDS
-// reads ahead, then per MFMA one read and four VALU instructions.
+// What bounds it: at many keys the board's power (the clock sits near 1.9 GHz)
+// and the softmax beside the products (VALU and MFMA each about 0.6 busy); at
+// 512 keys the queries and outputs on their way from and to HBM; at few items
+// the last, partly filled round of the chip.  Measured in turn on one card
+// through the entry point (transpose included) against one work-group per item
+// on 32x32x16 MFMAs: 32760 x 32760, 40 heads 18.1 -> 17.4 ms; 16896^2, 24 heads
+// (6.2 rounds) 3200 -> 2752 us; 4352^2, 48 heads (3.2 rounds) 517 -> 436 us;
+// 4608^2, 24 heads (1.7 rounds) 265 -> 255 us; 1536^2, 96 heads 170 -> 148 us;
+// 32760 x 512, 40 heads 491 -> 419 us; 5000^2, 3 heads 133 -> 72 us.
+//
+// One launch runs at most one work-group per CU (all of LDS) over a list of
+// (sequence, head, 256-query block) items; see Plan.  Per key tile t of an
+// item, one iteration issues the PV product of tile t - 1 and the score
+// product of tile t + 1 on MFMA together with the softmax of tile t (VALU),
+// which depends on neither.  Five LDS stages: tiles t - 1 (V), t, t + 1 (K),
+// t + 2 and t + 3 (in flight).  The copies run on through the list, so an
+// item starts on tiles that the previous one's last iterations fetched.
 constexpr int PSTAGE = 5;
+// The last round is shared out when that shortens the longest work-group by
+// this many tiles (about 1.7 us each): the second launch and the pieces' round
+// trip take 12-17 us at the shapes above.
+constexpr int SPLIT_MIN_TILES = 8;
+constexpr int NW = 8;          // waves per work-group, 32 queries each
+constexpr int QB = 32 * NW;    // queries per item
+constexpr int CPW = 16 / NW;   // 1 KB copies per wave for each of K and V^T
 
-// Work-groups are dispatched to the 8 XCDs round-robin (block b to XCD
-// b % 8); this maps block b to position x q + min(x, r) + b / 8 of n, so
-// that XCD x runs one contiguous range of positions.
-__device__ __forceinline__ int xcd_order(int b, int n) {
-  const int x = b & 7, q = n >> 3, r = n & 7;
-  return x * q + (x < r ? x : r) + (b >> 3);
-}
+// Items are numbered sequence-major, then head, then query block.  Work-groups
+// are dispatched to the 8 XCDs round-robin (block b to XCD b % 8); XCD x takes
+// one contiguous range of items, so that the work-groups that stream one
+// head's K and V at a time share an L2.  Its W work-groups take whole items in
+// rounds.  The last, partial round (rem items) is either one item each for rem
+// of them, or (split) its rem x ntiles key tiles in W contiguous shares: each
+// share covers a part of one item or of two, whose unnormalised outputs go to
+// the workspace for attn_combine_kernel.
+struct Plan {
+  int items, nqb, heads, ntiles;
+  int shares;  // most shares of an XCD's last round; 0: whole items
+};
 
-// Instruction-group order for the scheduler over one loop iteration: RA LDS
-// reads first, then per MFMA one read (while reads remain) and VG VALU ops.
-template <int RA, int VG, int NM, int ND>
-__device__ __forceinline__ void sched_pattern() {
-  __builtin_amdgcn_sched_group_barrier(0x100, RA, 0);  // DS read
-#pragma unroll
-  for (int i = 0; i < NM; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-    if (i < ND - RA) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, VG, 0);  // VALU
+struct Range {  // items of one XCD
+  int start, full, rem;
+  __host__ __device__ Range(int items, int x, int W) {
+    const int q = items >> 3, r = items & 7, cnt = q + (x < r ? 1 : 0);
+    start = x * q + (x < r ? x : r);
+    full = cnt / W;
+    rem = cnt % W;
   }
+};
+// First key tile (over the rem items) of share j.  A share has at least
+// SHARE_MIN_TILES tiles, so that writing and adding its piece (133 KB) stays
+// below the time of its products, and at most ntiles.
+constexpr int SHARE_MIN_TILES = 4;
+struct Shares {
+  int n;  // shares
+  int64_t units;
+  __host__ __device__ Shares(int rem, const Plan& p) {
+    units = (int64_t)rem * p.ntiles;
+    const int64_t most = units / SHARE_MIN_TILES;
+    n = most < rem ? rem : most < p.shares ? (int)most : p.shares;
+  }
+  __host__ __device__ int at(int j) const { return (int)(units * (j < n ? j : n) / n); }
+};
+
+// Partial output of a piece: O^T in register order (wave, 16 blocks of 16 d x
+// 16 queries, lane, 4 d), then the queries' row sums and running maxima.
+constexpr int PIECE_FLOATS = QB * D + 2 * QB;
+
+// Lanes l, l ^ 16, l ^ 32, l ^ 48 combined, by lane swaps on the VALU (a
+// shuffle through LDS would hold up the fragment reads).
+template <typename F>
+__device__ __forceinline__ float over_quarters(float v, F op) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const uint32_t u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const float w = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const uint32_t x = __float_as_uint(w);
+  const auto b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+#else
+  return v;
+#endif
+}
+__device__ __forceinline__ float max_quarters(float v) {
+  return over_quarters(v, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ float sum_quarters(float v) {
+  return over_quarters(v, [](float a, float b) { return a + b; });
 }
 
-template <int NW>
-__global__ __launch_bounds__(64 * NW) void flash_attn_pipe_kernel(
+// 16 bytes per lane from base + off (bytes, valid up to `bytes`; zeros past
+// it) into LDS at dst + 16 lane.
+__device__ __forceinline__ void copy16(const void* base, uint32_t bytes, lds_void_t* dst, uint32_t off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)bytes, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, off, 0, 0, 0);
+#endif
+}
+
+template <bool BOUNDED>
+__global__ __launch_bounds__(64 * NW) void flash_attn_kernel(
     const bf16_t* __restrict__ q, int64_t ldq, const bf16_t* __restrict__ k, int64_t ldk,
     const bf16_t* __restrict__ vt, int ldvt, bf16_t* __restrict__ o, int64_t ldo, int Lq, int Lk,
-    float scale_log2, SeqMap sm) {
+    float scale_log2, SeqMap sm, Plan pl, float* __restrict__ ws) {
   __shared__ __attribute__((aligned(1024))) char smem[PSTAGE * TILE_BYTES];  // [stage][K | V^T]
-  const RowMap rm = sm.at(blockIdx.z);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lq = lane >> 4;
 
-  constexpr int QB = NW * 32;
-  constexpr int CPW = 16 / NW;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lrow = lane & 31, lhalf = lane >> 5;
-  // grid.x runs over (head, query block), head-major, and each XCD takes a
-  // contiguous range of it: the work-groups that read one head's K and V
-  // share an L2
-  const int nqb = (Lq + QB - 1) / QB;
-  const int lt = xcd_order(blockIdx.x, gridDim.x);
-  const int h = lt / nqb;
-  const int q0 = (lt % nqb) * QB + wave * 32;
-  vt += (int64_t)blockIdx.z * (gridDim.x / nqb) * D * ldvt;
+  // this work-group's items: nfull whole ones, then its share of the rest
+  const int W = gridDim.x >> 3, j = blockIdx.x >> 3;
+  const Range rg(pl.items, blockIdx.x & 7, W);
+  const bool split = pl.shares && rg.rem;
+  const Shares sh(rg.rem, pl);
+  const int u0 = split ? sh.at(j) : 0, u1 = split ? sh.at(j + 1) : 0;
+  const int nfull = rg.full + (!split && j < rg.rem ? 1 : 0);
+  const int first_rest = u0 / pl.ntiles;  // of the rest
+  const int nseg = nfull + (u1 > u0 ? (u1 - 1) / pl.ntiles - first_rest + 1 : 0);
+  if (nseg == 0) return;
 
-  bf16x8_t qf[8];
-  {
-    const int qr = min(q0 + lrow, Lq - 1);
-    const bf16_t* qp = q + rm(qr) * ldq + h * D + 8 * lhalf;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) qf[s] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(qp + 16 * s));
-  }
-  const bf16_t* kh = k + h * D;
-  const bf16_t* vh = vt + (int64_t)h * D * ldvt;
-  // copies of tile t into the stage at byte offset so: K rows 4 ii .. 4 ii + 3
-  // and V^T rows 8 ii .. 8 ii + 7 for ii = CPW wave + j (any tile)
-  auto issue_tile = [&](int t, int so) {
-    const int kb0 = t * KT;
-    char* sk = smem + so;
-    char* sv = sk + KT * D * 2;
-#pragma unroll
-    for (int j = 0; j < CPW; ++j) {
-      const int ii = wave * CPW + j;
-      {
-        const int row = 4 * ii + (lane >> 4);
-        const int c = (lane & 15) ^ (row & 15);
-        const int key = min(kb0 + row, Lk - 1);
-        __builtin_amdgcn_global_load_lds((glb_void_t*)(kh + rm(key) * ldk + c * 8),
-                                         (lds_void_t*)(sk + ii * 1024), 16, 0, 0);
-      }
-      {
-        const int d = 8 * ii + (lane >> 3);
-        const int c = (lane & 7) ^ ((d >> 1) & 7);
-        __builtin_amdgcn_global_load_lds((glb_void_t*)(vh + (int64_t)d * ldvt + kb0 + c * 8),
-                                         (lds_void_t*)(sv + ii * 1024), 16, 0, 0);
-      }
-    }
+  struct Seg {
+    int z, h, q0, t0, n, piece;  // key tiles t0 .. t0 + n - 1; piece: workspace slot or -1
   };
-  // the same copies for a full tile on one side of the split: a uniform base
-  // per tile plus this lane's fixed byte offsets (32-bit: ldk, ldvt < 2^24)
-  const bool narrow = ldk < (1 << 24) && ldvt < (1 << 24);
-  const int ldk32 = narrow ? (int)ldk : 0, ldvt32 = narrow ? ldvt : 0;
+  auto segment = [&](int i) {
+    Seg s;
+    int item;
+    if (i < nfull) {
+      item = rg.start + i * W + j;
+      s.t0 = 0;
+      s.n = pl.ntiles;
+      s.piece = -1;
+    } else {
+      const int r = first_rest + i - nfull;
+      item = rg.start + rg.full * W + r;
+      s.t0 = max(u0 - r * pl.ntiles, 0);
+      s.n = min(u1 - r * pl.ntiles, pl.ntiles) - s.t0;
+      s.piece = s.n == pl.ntiles ? -1 : 2 * (int)blockIdx.x + i - nfull;
+    }
+    const int hb = item / pl.nqb;
+    s.q0 = (item - hb * pl.nqb) * QB;
+    s.z = hb / pl.heads;
+    s.h = hb - s.z * pl.heads;
+    return s;
+  };
+
+  // copies of a key tile: K rows 4 ii .. 4 ii + 3 and V^T rows 8 ii .. 8 ii + 7
+  // for ii = CPW wave + c.  A tile on one side of the split takes one uniform
+  // base and these per-lane byte offsets (32 bits: ldk, ldvt < 2^24); rows past
+  // the last key read zeros.
+  const bool narrow = ldk < (1 << 24) && ldvt < (1 << 24) && (sm.split >= Lk || sm.split % KT == 0);
   uint32_t kvo[CPW], vvo[CPW];
 #pragma unroll
-  for (int j = 0; j < CPW; ++j) {
-    const int ii = wave * CPW + j;
-    const int row = 4 * ii + (lane >> 4);
-    kvo[j] = (uint32_t)(row * ldk32 + (((lane & 15) ^ (row & 15)) << 3)) * 2u;
-    const int d = 8 * ii + (lane >> 3);
-    vvo[j] = (uint32_t)(d * ldvt32 + (((lane & 7) ^ ((d >> 1) & 7)) << 3)) * 2u;
+  for (int c = 0; c < CPW; ++c) {
+    const int ii = wave * CPW + c;
+    const int row = 4 * ii + (lane >> 4), d = 8 * ii + (lane >> 3);
+    kvo[c] = ((uint32_t)row * (narrow ? (uint32_t)ldk : 0) + (((lane & 15) ^ (row & 15)) << 3)) * 2u;
+    vvo[c] = ((uint32_t)d * (narrow ? (uint32_t)ldvt : 0) + (((lane & 7) ^ ((d >> 1) & 7)) << 3)) * 2u;
   }
-  auto issue_full = [&](int t, int so) {
-    const int kb0 = t * KT;
-    const char* kt0 = (const char*)(kh + rm(kb0) * ldk);
-    const char* vt0 = (const char*)(vh + kb0);
-    char* sk = smem + so;
+  // The copies' own place in the list, three tiles ahead of the products: tile
+  // ct of segment cs, its bases and bytes worked out an iteration ahead.  Past
+  // the end of the list (ci == nseg) the narrow form copies the last tile
+  // again, so that every iteration waits for the same number of copies.
+  int ci = 0, ct = 0;
+  Seg cs = segment(0);
+  struct {
+    uint32_t k_lo, k_hi, k_bytes, v_lo, v_hi;
+  } cp;
+  auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+  auto find_copy = [&](const Seg& s, int tile) {
+    const int kb0 = tile * KT;
+    const uint64_t kp = (uint64_t)(k + sm.at(s.z)(kb0)*ldk + s.h * D);
+    const uint64_t vp = (uint64_t)(vt + (int64_t)(s.z * pl.heads + s.h) * D * ldvt + kb0);
+    cp.k_lo = uniform((uint32_t)kp);
+    cp.k_hi = uniform((uint32_t)(kp >> 32));
+    cp.v_lo = uniform((uint32_t)vp);
+    cp.v_hi = uniform((uint32_t)(vp >> 32));
+    cp.k_bytes = uniform((uint32_t)(min(Lk - kb0, KT) - 1) * (uint32_t)ldk * 2u + 2u * D);
+  };
+  // NARROW: known to be.  (The middle iterations hold no global_load_lds: the
+  // compiler counts one as an LDS event that may return out of order, and
+  // then waits for every LDS read instead of the oldest.)
+  auto issue = [&](int so, auto narrow_) {
+    constexpr bool NARROW = decltype(narrow_)::value;
+    char* sk = smem + so + wave * CPW * 1024;
     char* sv = sk + KT * D * 2;
+    if (NARROW || narrow) {
+      const void* kt = (const void*)(((uint64_t)cp.k_hi << 32) | cp.k_lo);
+      const void* vh = (const void*)(((uint64_t)cp.v_hi << 32) | cp.v_lo);
 #pragma unroll
-    for (int j = 0; j < CPW; ++j) {
-      const int ii = wave * CPW + j;
-      __builtin_amdgcn_global_load_lds((glb_void_t*)(kt0 + kvo[j]), (lds_void_t*)(sk + ii * 1024), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((glb_void_t*)(vt0 + vvo[j]), (lds_void_t*)(sv + ii * 1024), 16, 0, 0);
+      for (int c = 0; c < CPW; ++c) {
+        copy16(kt, cp.k_bytes, (lds_void_t*)(sk + c * 1024), kvo[c]);
+        copy16(vh, 0xffffffffu, (lds_void_t*)(sv + c * 1024), vvo[c]);
+      }
+    } else if (ci < nseg) {
+      const RowMap rm = sm.at(cs.z);
+      const int kb0 = (cs.t0 + ct) * KT;
+      const bf16_t* kh = k + cs.h * D;
+      const bf16_t* vh = vt + (int64_t)(cs.z * pl.heads + cs.h) * D * ldvt + kb0;
+#pragma unroll
+      for (int c = 0; c < CPW; ++c) {
+        const int ii = wave * CPW + c;
+        const int row = 4 * ii + (lane >> 4), d = 8 * ii + (lane >> 3);
+        __builtin_amdgcn_global_load_lds(
+            (glb_void_t*)(kh + rm(min(kb0 + row, Lk - 1)) * ldk + (((lane & 15) ^ (row & 15)) << 3)),
+            (lds_void_t*)(sk + c * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((glb_void_t*)(vh + (int64_t)d * ldvt + (((lane & 7) ^ ((d >> 1) & 7)) << 3)),
+                                         (lds_void_t*)(sv + c * 1024), 16, 0, 0);
+      }
     }
   };
-  // this lane's fragment offsets inside a stage: K per s (kb = 1 adds 8 KB),
-  // V^T per ks (dt adds 4 KB each)
-  int koff[8], voff[4];
-#pragma unroll
-  for (int s = 0; s < 8; ++s) koff[s] = k_off(lrow, 2 * s + lhalf);
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) voff[ks] = KT * D * 2 + v_off(lrow, 2 * ks + lhalf);
-  auto scores = [&](int so, f32x16_t (&sacc)[2]) {
-    const char* sk = smem + so;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[kb][r] = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sk + koff[s] + kb * 32 * 256));
-        sacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc[kb], 0, 0, 0);
-      }
+  auto issued = [&]() {  // on to the next tile
+    if (ci == nseg) return;
+    if (ct + 1 < cs.n) {
+      ++ct;
+    } else if (++ci < nseg) {
+      cs = segment(ci);
+      ct = 0;
+    }
+    find_copy(cs, cs.t0 + ct);
   };
-  f32x16_t oacc[4];
+  find_copy(cs, cs.t0);
+
+  // Fragments (16x16x32).  Q^T (B operand): d = 32 s + 8 lq + [0, 8) of query
+  // 16 g + lr.  K (A): key 16 kb + lr, the same d.  S^T: query lr, keys 4 lq +
+  // [0, 4) of block kb.  P^T (B): blocks 2 ks and 2 ks + 1 of a lane side by
+  // side, so slot 8 lq + e of a 32-key group is key 16 (e >> 2) + 4 lq + (e & 3):
+  // the key order of V^T (A: row d = 16 dt + lr, slots 32 ks + 8 lq + [0, 8)).
+  bf16x8_t qf[2][4];
+  auto load_q = [&](const Seg& s) {
+    const RowMap rm = sm.at(s.z);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int g = 0; g < 2; ++g) {
+      const bf16_t* qp = q + rm(min(s.q0 + 32 * wave + 16 * g + lr, Lq - 1)) * ldq + s.h * D + 8 * lq;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
-  float l_run = 0.f;
-  const float mneg = -BOUNDED_SHIFT_LOG2;
+      for (int t = 0; t < 4; ++t) qf[g][t] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(qp + 32 * t));
+    }
+  };
+  int koff[4], voff[2];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) koff[s] = k_off(lr, 4 * s + lq);
+#pragma unroll
+  for (int s = 0; s < 2; ++s) voff[s] = KT * D * 2 + v_off(lr, 4 * s + lq);
+  // A tile's fragments in the order of their use: V^T 0..15 (two d blocks, then
+  // their k-steps) and K 0..15 (two key blocks, then their d steps), so that
+  // four independent accumulators stand between the steps of a dependent chain.
+  auto v_dt = [](int i) { return 2 * (i >> 2) + (i & 1); };
+  auto v_ks = [](int i) { return (i >> 1) & 1; };
+  auto k_kb = [](int i) { return 2 * (i >> 3) + (i & 1); };
+  auto k_s = [](int i) { return (i >> 1) & 3; };
+  auto v_frag = [&](int so, int i) {
+    return __builtin_bit_cast(bf16x8_t, *(const uint4*)(smem + so + voff[v_ks(i)] + v_dt(i) * 16 * 128));
+  };
+  auto k_frag = [&](int so, int i) {
+    return __builtin_bit_cast(bf16x8_t, *(const uint4*)(smem + so + koff[k_s(i)] + k_kb(i) * 16 * 256));
+  };
+  auto scores_step = [&](int i, const bf16x8_t& kf, f32x4_t (&sacc)[4][2]) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      f32x4_t& c = sacc[k_kb(i)][g];
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[g][k_s(i)], k_s(i) ? c : f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    }
+  };
+  auto scores = [&](int so, f32x4_t (&sacc)[4][2]) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) scores_step(i, k_frag(so, i), sacc);
+  };
+  f32x4_t oacc[8][2];
+  float m_run[2], l_run[2];
   const bf16x2_t ones = {(__bf16)1.f, (__bf16)1.f};
-  auto softmax = [&](int t, f32x16_t (&sacc)[2], bf16x8_t (&pf)[4], bool ragged) {
-    const int kbase = t * KT;
-    if (ragged) {
+  auto mask = [&](int t, f32x4_t (&sacc)[4][2]) {  // keys past the last one
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = kbase + kb * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3);
-          if (key >= Lk) sacc[kb][r] = -INFINITY;
-        }
-    }
-    float ls = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      uint32_t w[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kb][2 * j], scale_log2, mneg));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kb][2 * j + 1], scale_log2, mneg));
-        w[j] = pack_bf16x2(p0, p1);
-        ls = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w[j]), ones, ls, false);
-      }
-      pf[2 * kb] = __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
-      pf[2 * kb + 1] = __builtin_bit_cast(bf16x8_t, make_uint4(w[4], w[5], w[6], w[7]));
-    }
-    l_run += ls;
+      for (int r = 0; r < 4; ++r)
+        if (t * KT + kb * 16 + 4 * lq + r >= Lk) sacc[kb][0][r] = sacc[kb][1][r] = -INFINITY;
   };
-  auto pv = [&](int so, const bf16x8_t (&pf)[4]) {
-    const char* sv = smem + so;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sv + voff[ks] + dt * 32 * 128));
-        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks], oacc[dt], 0, 0, 0);
-      }
+  // running maximum (kept unless the new one is more than RESCALE_SLACK above
+  // it: softmax is shift invariant); rescales what has been accumulated
+  auto tile_max = [&](const f32x4_t (&sacc)[4][2], int i, float (&mx)[2]) {  // its step i of 16
+    const f32x4_t& c = sacc[i & 3][i >> 3];
+    mx[i >> 3] = fmaxf(mx[i >> 3], fmaxf(c[2 * ((i >> 2) & 1)], c[2 * ((i >> 2) & 1) + 1]));
   };
-  const int ntiles = (Lk + KT - 1) / KT;
-  // steady copies need every full tile on one side of the split and 32-bit
-  // lane offsets
-  const bool fast = (rm.split >= Lk || rm.split % KT == 0) && narrow;
-  f32x16_t sb[2][2];
-  bf16x8_t pb[2][4];
-  // stage byte offsets of tiles t - 1 (PV), t + 1 (scores) and t + 3 (copies)
-  // at iteration t, advanced once per iteration
+  auto raise_max = [&](float (&mx)[2]) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) mx[g] = max_quarters(mx[g]) * scale_log2;
+    const bool need = mx[0] > m_run[0] + RESCALE_SLACK || mx[1] > m_run[1] + RESCALE_SLACK;
+    if (__builtin_amdgcn_ballot_w64(need)) {
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const float m_new = mx[g] > m_run[g] + RESCALE_SLACK ? mx[g] : m_run[g];
+        const float alpha = __builtin_amdgcn_exp2f(m_run[g] - m_new);
+        l_run[g] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) oacc[dt][g][r] *= alpha;
+        m_run[g] = m_new;
+      }
+    }
+  };
+  // probability e of a lane's 32; the row sum takes exactly the rounded values
+  // that the second product uses
+  struct Soft {
+    float p0, ls, sum[2];
+    uint32_t w[4];
+  };
+  auto softmax_step = [&](int e, const f32x4_t (&sacc)[4][2], bf16x8_t (&pf)[2][2], Soft& x) {
+    const int g = e >> 4, ks = (e >> 3) & 1, i = e & 7;
+    const float mneg = BOUNDED ? -BOUNDED_SHIFT_LOG2 : -m_run[g];
+    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[2 * ks + (i >> 2)][g][i & 3], scale_log2, mneg));
+    if (!(e & 1)) {
+      x.p0 = p;
+      return;
+    }
+    x.w[i >> 1] = pack_bf16x2(x.p0, p);
+    // formed here: the branches at an iteration's end would otherwise draw the
+    // whole softmax past the barrier, away from the MFMAs
+    asm volatile("" : "+v"(x.w[i >> 1]));
+    x.ls = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, x.w[i >> 1]), ones, (e & 15) == 1 ? 0.f : x.ls,
+                                           false);
+    if (i == 7) pf[ks][g] = __builtin_bit_cast(bf16x8_t, make_uint4(x.w[0], x.w[1], x.w[2], x.w[3]));
+    if (i == 7 && ks == 1) x.sum[g] = x.ls;
+  };
+  auto pv_step = [&](int i, const bf16x8_t& vf, const bf16x8_t (&pf)[2][2]) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+      oacc[v_dt(i)][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[v_ks(i)][g], oacc[v_dt(i)][g], 0, 0, 0);
+  };
+  auto pv = [&](int so, const bf16x8_t (&pf)[2][2]) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) pv_step(i, v_frag(so, i), pf);
+  };
+
+  f32x4_t sb[2][4][2];
+  bf16x8_t pb[2][2][2];
+  // stage byte offsets of tiles t - 1 (PV), t (this one), t + 1 (scores) and
+  // t + 3 (copies), advanced once per iteration
   constexpr int RING = PSTAGE * TILE_BYTES;
   int so_pv = (PSTAGE - 1) * TILE_BYTES, so_sc = TILE_BYTES, so_is = 3 * TILE_BYTES;
+  auto next = [](int so) { return so + TILE_BYTES == RING ? 0 : so + TILE_BYTES; };
   auto advance = [&]() {
-    so_pv = so_pv + TILE_BYTES == RING ? 0 : so_pv + TILE_BYTES;
-    so_sc = so_sc + TILE_BYTES == RING ? 0 : so_sc + TILE_BYTES;
-    so_is = so_is + TILE_BYTES == RING ? 0 : so_is + TILE_BYTES;
+    so_pv = next(so_pv);
+    so_sc = next(so_sc);
+    so_is = next(so_is);
   };
-  // iteration t, buffers by the parity P of t: copies of tile t + 3; PV of
-  // tile t - 1; scores of t + 1; softmax of t; then tile t + 2 has landed
-  // (tile t + 3 may stay in flight) and every wave is done with tile t - 1
-  auto iter_any = [&](auto par_, int t) {
-    constexpr int P = decltype(par_)::value;
-    if (t + 3 < ntiles) issue_tile(t + 3, so_is);
-    if (t > 0) pv(so_pv, pb[P ^ 1]);
-    if (t + 1 < ntiles) scores(so_sc, sb[P ^ 1]);
-    softmax(t, sb[P], pb[P], t * KT + KT > Lk);
-    if (t + 3 < ntiles) __builtin_amdgcn_s_waitcnt((2 * CPW) | (7 << 4) | (0 << 8));
-    else __builtin_amdgcn_s_waitcnt(0);
+  auto store_out = [&](const Seg& s) {
+    if (s.piece < 0) {
+      const RowMap rm = sm.at(s.z);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const int qi = s.q0 + 32 * wave + 16 * g + lr;
+        const float inv = 1.f / sum_quarters(l_run[g]);
+        if (qi < Lq) {
+          bf16_t* op = o + rm(qi) * ldo + s.h * D + 4 * lq;
+#pragma unroll
+          for (int dt = 0; dt < 8; ++dt)
+            *(uint2*)(op + 16 * dt) = make_uint2(pack_bf16x2(oacc[dt][g][0] * inv, oacc[dt][g][1] * inv),
+                                                 pack_bf16x2(oacc[dt][g][2] * inv, oacc[dt][g][3] * inv));
+        }
+      }
+    } else {
+      float* w = ws + (int64_t)s.piece * PIECE_FLOATS;
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt)
+          *(f32x4_t*)(w + ((wave * 16 + 8 * g + dt) * 64 + lane) * 4) = oacc[dt][g];
+        const float l = sum_quarters(l_run[g]);
+        if (lq == 0) {
+          w[QB * D + 32 * wave + 16 * g + lr] = l;
+          w[QB * D + QB + 32 * wave + 16 * g + lr] = m_run[g];
+        }
+      }
+    }
+  };
+
+  // End of an iteration: the copies before this one's have landed (vmcnt(4), or
+  // vmcnt(20) while the 16 stores of an output stand between the two), LDS
+  // reads are down to LGKM, and the work-groups' waves meet.
+  int stores = 0;  // iterations in which the copies waited for are older than the stores
+  auto meet = [&](auto lgkm_, auto narrow_) {
+    constexpr int LGKM = decltype(lgkm_)::value;
+    if (!decltype(narrow_)::value && !narrow) {
+      __builtin_amdgcn_s_waitcnt(0);
+    } else if (stores > 0) {
+      __builtin_amdgcn_s_waitcnt((20 & 15) | (7 << 4) | (LGKM << 8) | ((20 >> 4) << 14));
+      --stores;
+    } else {
+      __builtin_amdgcn_s_waitcnt((2 * CPW) | (7 << 4) | (LGKM << 8));
+    }
     asm volatile("s_barrier" ::: "memory");
     advance();
+    issued();
   };
-  // 1 <= t, t + 4 < ntiles - 1: tiles t and t + 3 full, no guard
-  auto iter_steady = [&](auto par_, int t) {
+  // Iteration over tile t of the n of segment s.  In: its scores in sb[0], the
+  // probabilities of the tile before it in pb[0]; out: the same for the next
+  // tile.  At its end tile t + 2 has landed (tile t + 3 may stay in flight) and
+  // every wave is done with tile t - 1.
+  int si = 0;  // this segment's place in the list
+  Seg s = cs;
+  int t = 0;
+  // Any tile, one product after the other.  Before tile 0 stands the last
+  // segment's PV product, whose output then leaves; after tile n - 1 the next
+  // segment's first scores.
+  Seg prev{};
+  auto iter_edge = [&]() {
+    const bool last = t + 1 == s.n, end = last && si + 1 == nseg;
+    Seg nxt = s;
+    if (last && !end) {
+      nxt = segment(si + 1);
+      load_q(nxt);
+    }
+    issue(so_is, std::false_type{});
+    if (t > 0 || si > 0) pv(so_pv, pb[0]);
+    if (t == 0) {
+      if (si > 0) {
+        store_out(prev);
+        // both query groups of the wave stored: 16 or 20 instructions
+        stores = prev.piece >= 0 || prev.q0 + 32 * wave + 16 < Lq ? 2 : 0;
+      }
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) oacc[dt][0] = oacc[dt][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        m_run[g] = BOUNDED ? BOUNDED_SHIFT_LOG2 : -INFINITY;
+        l_run[g] = 0.f;
+      }
+    }
+    if ((s.t0 + t + 1) * KT > Lk) mask(s.t0 + t, sb[0]);
+    if constexpr (!BOUNDED) {
+      float mx[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) tile_max(sb[0], i, mx);
+      raise_max(mx);
+    }
+    Soft x;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) softmax_step(e, sb[0], pb[0], x);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) l_run[g] += x.sum[g];
+    if (!end) scores(so_sc, sb[0]);
+    meet(std::integral_constant<int, 0>{}, std::false_type{});
+    ++t;
+    if (last) {
+      prev = s;
+      s = nxt;
+      t = 0;
+      ++si;
+    }
+  };
+  // 1 <= t, t + 1 < n (so t is full), bounded logits: with the two buffers of
+  // each kind in turn (P), in 32 fenced steps of two MFMAs, one
+  // fragment read AHEAD steps before its use (the last ones for the next
+  // iteration: V^T of tile t, across the barrier) and 1/32 of the softmax; the
+  // fences keep the reads ahead (left to the scheduler each read stood right
+  // before its MFMAs).
+  constexpr int AHEAD = 4;
+  bf16x8_t fr[AHEAD];
+  auto iter_mid = [&](auto par_) {
     constexpr int P = decltype(par_)::value;
-    issue_full(t + 3, so_is);
-    pv(so_pv, pb[P ^ 1]);
-    scores(so_sc, sb[P ^ 1]);
-    softmax(t, sb[P], pb[P], false);
-    sched_pattern<3, 4, 32, 32>();
-    __builtin_amdgcn_s_waitcnt((2 * CPW) | (7 << 4) | (0 << 8));
-    asm volatile("s_barrier" ::: "memory");
-    advance();
+    issue(so_is, std::true_type{});
+    const int so_t = next(so_pv);
+    Soft x;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      if (i < 16) pv_step(i, fr[i % AHEAD], pb[P]);
+      else scores_step(i - 16, fr[i % AHEAD], sb[P ^ 1]);
+      const int n = i + AHEAD;
+      fr[i % AHEAD] = n < 16 ? v_frag(so_pv, n) : n < 32 ? k_frag(so_sc, n - 16) : v_frag(so_t, n - 32);
+      softmax_step(i, sb[P], pb[P ^ 1], x);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g) l_run[g] += x.sum[g];
+    // the fragment reads still in flight are of tile t, which stays for another iteration
+    meet(std::integral_constant<int, 15>{}, std::true_type{});
+    ++t;
   };
-  for (int u = 0; u < 3 && u < ntiles; ++u) issue_tile(u, u * TILE_BYTES);
+  // The same tiles without a bound, one product after the other: the running
+  // maximum stands between them, and a second set of buffers would spill.
+  auto iter_mid_max = [&]() {
+    issue(so_is, std::true_type{});
+    pv(so_pv, pb[0]);
+    float mx[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tile_max(sb[0], i, mx);
+    raise_max(mx);
+    Soft x;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) softmax_step(e, sb[0], pb[0], x);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) l_run[g] += x.sum[g];
+    scores(so_sc, sb[0]);
+    meet(std::integral_constant<int, 0>{}, std::true_type{});
+    ++t;
+  };
+  load_q(s);
+  for (int u = 0; u < 3; ++u) {
+    issue(u * TILE_BYTES, std::false_type{});
+    issued();
+  }
   // tiles 0 and 1 have landed (tile 2 may stay in flight)
-  if (ntiles >= 3) __builtin_amdgcn_s_waitcnt((2 * CPW) | (7 << 4) | (0 << 8));
+  if (narrow) __builtin_amdgcn_s_waitcnt((2 * CPW) | (7 << 4) | (0 << 8));
   else __builtin_amdgcn_s_waitcnt(0);
   asm volatile("s_barrier" ::: "memory");
   scores(0, sb[0]);
-  iter_any(std::integral_constant<int, 0>{}, 0);
-  int t = 1;
-  for (; fast && t + 5 < ntiles; t += 2) {
-    iter_steady(std::integral_constant<int, 1>{}, t);
-    iter_steady(std::integral_constant<int, 0>{}, t + 1);
-  }
-  for (; t < ntiles; t += 2) {
-    iter_any(std::integral_constant<int, 1>{}, t);
-    if (t + 1 < ntiles) iter_any(std::integral_constant<int, 0>{}, t + 1);
-  }
-  // so_pv now holds tile ntiles - 1
-  if ((ntiles - 1) & 1) pv(so_pv, pb[1]);
-  else pv(so_pv, pb[0]);
-
-  {
-    const int qi = q0 + lrow;
-    const float l = l_run + __shfl_xor(l_run, 32, 64);
-    const float inv = 1.f / l;
-    if (qi < Lq) {
-      bf16_t* op = o + rm(qi) * ldo + h * D;
+  while (si < nseg) {
+    if constexpr (BOUNDED) {
+      if (narrow && t > 0 && t + 2 < s.n) {  // two tiles inside the segment
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int d0 = dt * 32 + 8 * r4 + 4 * lhalf;
-          *(uint2*)(op + d0) = make_uint2(pack_bf16x2(oacc[dt][4 * r4] * inv, oacc[dt][4 * r4 + 1] * inv),
-                                          pack_bf16x2(oacc[dt][4 * r4 + 2] * inv, oacc[dt][4 * r4 + 3] * inv));
-        }
+        for (int f = 0; f < AHEAD; ++f) fr[f] = v_frag(so_pv, f);
+        do {
+          iter_mid(std::integral_constant<int, 0>{});
+          iter_mid(std::integral_constant<int, 1>{});
+        } while (t + 2 < s.n);
+      }
+    } else if (narrow && t > 0) {
+      while (t + 1 < s.n) iter_mid_max();
     }
+    iter_edge();
   }
+  pv(so_pv, pb[0]);
+  store_out(prev);
 }
 
-// vt[h][d][16 g + vt_slot(k)] = v[16 g + k][h*128 + d] for keys < Lk, 0 up to ldvt.
+// Adds the pieces of the shared items in the order of their keys and stores
+// the normalised output.  blockIdx.x: XCD (8) x shared item; blockIdx.y: the
+// item's 16-query group; each of the four waves takes two of its 16-wide d blocks.
+__global__ __launch_bounds__(256) void attn_combine_kernel(bf16_t* __restrict__ o, int64_t ldo, int Lq, SeqMap sm,
+                                                           Plan pl, int W, const float* __restrict__ ws) {
+  const int x = blockIdx.x & 7, r = blockIdx.x >> 3;
+  const Range rg(pl.items, x, W);
+  if (r >= rg.rem) return;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4, dt0 = 2 * (threadIdx.x >> 6);
+  const Shares sh(rg.rem, pl);
+  // shares j0 .. j1 - 1 hold this item's tiles [r ntiles, (r + 1) ntiles)
+  const int ub = r * pl.ntiles, ue = ub + pl.ntiles;
+  int j0 = (int)((int64_t)ub * sh.n / sh.units);
+  while (sh.at(j0 + 1) <= ub) ++j0;
+  if (sh.at(j0) <= ub && sh.at(j0 + 1) >= ue) return;  // one share's whole item: stored already
+  int j1 = j0 + 1;
+  while (sh.at(j1) < ue) ++j1;
+  auto piece = [&](int j) {
+    return ws + (int64_t)(2 * (8 * j + x) + r - sh.at(j) / pl.ntiles) * PIECE_FLOATS;
+  };
+  const int wg = blockIdx.y, qw = 16 * wg + lr;
+  float m = -INFINITY, l = 0.f;
+  for (int j = j0; j < j1; ++j) m = fmaxf(m, piece(j)[QB * D + QB + qw]);
+  f32x4_t acc[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+  constexpr int U = 4;  // pieces whose loads are in flight together
+  for (int j = j0; j < j1; j += U) {
+    f32x4_t v[U][2];
+    float a[U], lv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float* w = piece(min(j + u, j1 - 1));
+      a[u] = w[QB * D + QB + qw];
+      lv[u] = w[QB * D + qw];
+#pragma unroll
+      for (int d = 0; d < 2; ++d) v[u][d] = *(const f32x4_t*)(w + ((wg * 8 + dt0 + d) * 64 + lane) * 4);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (j + u >= j1) break;
+      const float f = __builtin_amdgcn_exp2f(a[u] - m);
+      l += f * lv[u];
+#pragma unroll
+      for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[d][e] += f * v[u][d][e];
+    }
+  }
+  const int item = rg.start + rg.full * W + r, hb = item / pl.nqb;
+  const int z = hb / pl.heads, h = hb - z * pl.heads;
+  const int qi = (item - hb * pl.nqb) * QB + qw;
+  if (qi >= Lq) return;
+  const float inv = 1.f / l;
+  bf16_t* op = o + sm.at(z)(qi)*ldo + h * D + 16 * dt0 + 4 * lq;
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+    *(uint2*)(op + 16 * d) = make_uint2(pack_bf16x2(acc[d][0] * inv, acc[d][1] * inv),
+                                        pack_bf16x2(acc[d][2] * inv, acc[d][3] * inv));
+}
+
+// vt[h][d][32 g + vt_slot(k)] = v[32 g + k][h*128 + d] for keys < Lk, 0 up to ldvt.
+// 16-byte reads of a 64 x 128 tile into LDS rows of 65 words, then eight
+// halves down a column per 16-byte write: 8 x 8 (key run, d) lanes read 8
+// different banks' words in each of the steps.
 __global__ __launch_bounds__(256) void transpose_v_kernel(const bf16_t* __restrict__ v, int64_t ldv,
                                                           bf16_t* __restrict__ vt, int Lk, int ldvt, SeqMap sm) {
-  __shared__ bf16_t tile[64][D + 2];
+  __shared__ uint32_t tile[64][D / 2 + 1];
   const RowMap rm = sm.at(blockIdx.z);
   vt += (int64_t)blockIdx.z * gridDim.y * D * ldvt;
   const int l0 = blockIdx.x * 64, h = blockIdx.y, tid = threadIdx.x;
-  for (int i = tid; i < 64 * (D / 2); i += 256) {
-    const int r = i / (D / 2), c2 = i % (D / 2);
-    const int l = l0 + r;
-    uint32_t w = 0;
-    if (l < Lk) w = *(const uint32_t*)(v + rm(l) * ldv + h * D + 2 * c2);
-    const int rs = (r & ~15) | vt_slot(r & 15);
-    tile[rs][2 * c2] = (bf16_t)(w & 0xffff);
-    tile[rs][2 * c2 + 1] = (bf16_t)(w >> 16);
+  const bool wide = !(((uintptr_t)v | (uintptr_t)(2 * ldv)) & 15);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int i = tid + 256 * j, r = i / 16, c = i % 16;
+    uint32_t w[4] = {0, 0, 0, 0};
+    if (l0 + r < Lk) {
+      const bf16_t* p = v + rm(l0 + r) * ldv + h * D + 8 * c;
+      if (wide) {
+        const uint4 u = *(const uint4*)p;
+        w[0] = u.x; w[1] = u.y; w[2] = u.z; w[3] = u.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = p[2 * e] | ((uint32_t)p[2 * e + 1] << 16);
+      }
+    }
+    const int rs = (r & ~31) | vt_slot(r & 31);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tile[rs][4 * c + e] = w[e];
   }
   __syncthreads();
   bf16_t* out = vt + (int64_t)h * D * ldvt + l0;
-  for (int i = tid; i < D * 32; i += 256) {
-    const int d = i / 32, c2 = i % 32;
-    const uint32_t w = (uint32_t)tile[2 * c2][d] | ((uint32_t)tile[2 * c2 + 1][d] << 16);
-    *(uint32_t*)(out + (int64_t)d * ldvt + 2 * c2) = w;
+  const int run = tid & 7;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int d = (tid >> 3) + 32 * j, sh = 16 * (d & 1);
+    uint32_t x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = (tile[8 * run + e][d / 2] >> sh) & 0xffffu;
+    *(uint4*)(out + (int64_t)d * ldvt + 8 * run) =
+        make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16));
   }
 }
 
@@ -605,28 +752,48 @@ hipError_t launch_transpose_v_bf16(const void* v, int64_t ldv, void* vt, int Lk,
   return hipGetLastError();
 }
 
+namespace {
+// Work-groups per XCD: one per CU.
+int attn_width(int n_cu) { return std::max(1, n_cu / 8); }
+
+Plan attn_plan(int Lq, int Lk, int heads, int nseq, int W) {
+  Plan p;
+  p.nqb = (Lq + QB - 1) / QB;
+  p.heads = heads;
+  p.items = nseq * heads * p.nqb;
+  p.ntiles = (Lk + KT - 1) / KT;
+  p.shares = W;
+  // key tiles that the longest work-group saves by sharing the last round
+  const int most = (p.items + 7) / 8, rem = most % W;
+  const int64_t longest = rem ? (Shares(rem, p).units + Shares(rem, p).n - 1) / Shares(rem, p).n : 0;
+  if (!rem || p.ntiles - longest < SPLIT_MIN_TILES) p.shares = 0;
+  return p;
+}
+}  // namespace
+
+size_t flash_attn_ws_bytes(int Lq, int Lk, int heads, int nseq, int n_cu) {
+  const int W = attn_width(n_cu);
+  return attn_plan(Lq, Lk, heads, nseq, W).shares ? (size_t)16 * W * PIECE_FLOATS * sizeof(float) : 0;
+}
+
 hipError_t launch_flash_attn_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk,
                                   const void* vt, int ldvt, void* o, int64_t ldo, int Lq, int Lk,
-                                  int heads, bool bounded_logits, hipStream_t s, int split, int64_t gap,
-                                  int nseq, int64_t zs, int64_t gz) {
+                                  int heads, bool bounded_logits, hipStream_t s, int n_cu, float* ws, int split,
+                                  int64_t gap, int nseq, int64_t zs, int64_t gz) {
   if (nseq < 1 || Lq < 1 || Lk < 1) return hipErrorInvalidValue;
-  // 32 queries per wave, 8 waves: about 190 registers per lane, so two
-  // waves share each SIMD and one wave's softmax overlaps the other's MFMAs.
-  constexpr int kQG = 1, kNW = 8;
-  constexpr int QB = 32 * kQG * kNW;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)D);
-  const dim3 grid((Lq + QB - 1) / QB, heads, nseq);
   const SeqMap sm{split, gap, gz, zs};
-  // bounded logits take the software-pipelined kernel, the others the
-  // single-stage kernel with a running maximum
-  if (bounded_logits)
-    hipLaunchKernelGGL((flash_attn_pipe_kernel<kNW>), dim3(grid.x * heads, 1, nseq), dim3(64 * kNW), 0, s,
-                       (const bf16_t*)q, ldq, (const bf16_t*)k, ldk, (const bf16_t*)vt, ldvt, (bf16_t*)o, ldo, Lq,
-                       Lk, scale_log2, sm);
-  else
-    hipLaunchKernelGGL((flash_attn_bf16_kernel<false, kQG, kNW>), grid, dim3(64 * kNW), 0, s,
-                       (const bf16_t*)q, ldq, (const bf16_t*)k, ldk, (const bf16_t*)vt, ldvt, (bf16_t*)o,
-                       ldo, Lq, Lk, scale_log2, sm);
+  int W = attn_width(n_cu);
+  Plan p = attn_plan(Lq, Lk, heads, nseq, W);
+  if (!ws) p.shares = 0;
+  if (!p.shares) W = std::min(W, (p.items + 7) / 8);
+  hipLaunchKernelGGL(bounded_logits ? flash_attn_kernel<true> : flash_attn_kernel<false>, dim3(8 * W), dim3(64 * NW), 0,
+                     s, (const bf16_t*)q, ldq, (const bf16_t*)k, ldk, (const bf16_t*)vt, ldvt, (bf16_t*)o, ldo, Lq, Lk,
+                     scale_log2, sm, p, ws);
+  if (p.shares) {
+    const int rest = std::max(Range(p.items, 0, W).rem, Range(p.items, 7, W).rem);
+    hipLaunchKernelGGL(attn_combine_kernel, dim3(8 * rest, 2 * NW), dim3(256), 0, s, (bf16_t*)o, ldo, Lq, sm, p, W, ws);
+  }
   return hipGetLastError();
 }
 

@@ -118,6 +118,7 @@ struct dit_cache {
   void* Y = nullptr;       // [cap_seq L, 4H+F]: q | k | v | attn out | mlp hidden
   void* vt = nullptr;      // bf16 [cap_seq, heads, 128, round_up(L, 64)]
   float* modq = nullptr;   // f32 [cap_seq, n_mod]: gathered modulation vectors of one step
+  float* attn_ws = nullptr;  // pieces of shared attention items (flash_attn_ws_bytes), or nullptr
   void* yf = nullptr;      // [N, H] final-layer input
   float* vel = nullptr;    // f32 [nb, N, C]
   float* ones = nullptr;   // f32 [H] (ungated residual)
@@ -309,7 +310,7 @@ dit_status attention(dit_cache* c, const void* q, int64_t ldq, const void* k, in
     Scope s(c, DIT_K_ATTN, flops);
     // q and k leave the projection through a unit-gain RMS norm: bounded logits
     HIPCK(dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt_ws, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads,
-                                      true, c->stream, split, gap, nseq, zs, gz));
+                                      true, c->stream, c->n_cu, c->attn_ws, split, gap, nseq, zs, gz));
   } else {
     if (nseq != 1) return fail(c, DIT_EINVAL, "f32 attention runs one sequence per launch");
     Scope s(c, DIT_K_ATTN, flops);
@@ -469,6 +470,12 @@ dit_status ensure_seq(dit_cache* c, int Q) {
     HIPCK(hipMemsetAsync(c->vt, 0, vb, c->stream));
   }
   if (c->stacked && c->cfg.pooled_text) TRY(dalloc(c, &c->modq, (size_t)Q * c->n_mod * 4));
+  if (c->bf16 && !c->attn_ws) {  // one size, whatever the launch; any subset of the sequences may compute
+    const int heads = c->cfg.heads;
+    size_t need = c->cfg.n_cross ? dit::flash_attn_ws_bytes(c->N, c->Nt, heads, 1, c->n_cu) : 0;
+    for (int n = 1; n <= Q; ++n) need = std::max(need, dit::flash_attn_ws_bytes(c->L, c->L, heads, n, c->n_cu));
+    if (need) TRY(dalloc(c, &c->attn_ws, need));
+  }
   c->cap_seq = Q;
   return DIT_OK;
 }
@@ -1630,7 +1637,7 @@ void dit_cache_destroy(dit_cache* c) {
   if (c->stream) hipStreamSynchronize(c->stream);
   free_per_call(c);
   for (Lane& l : c->lanes) free_lane(l);
-  void* ps[] = {c->wdev, c->xs, c->X, c->A, c->Y, c->vt, c->modq, c->yf, c->vel, c->ones,
+  void* ps[] = {c->wdev, c->xs, c->X, c->A, c->Y, c->vt, c->modq, c->attn_ws, c->yf, c->vel, c->ones,
                 c->partials, c->cand, c->st_hi, c->st_lo};
   for (void* p : ps)
     if (p) hipFree(p);
@@ -1689,74 +1696,126 @@ dit_status dit_gemm_bf16(const dit_gemm_desc* d, void* hip_stream) {
   return DIT_OK;
 }
 
-dit_status dit_attention_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v, int64_t ldv,
-                              void* o, int64_t ldo, int32_t Lq, int32_t Lk, int32_t heads, int32_t flags,
-                              void* vt_ws, void* hip_stream) {
-  dit_cache* c = nullptr;
-  if (!q || !k || !v || !o || !vt_ws) return fail(c, DIT_EINVAL, "null argument");
-  if (Lq < 1 || Lk < 1 || heads < 1) return fail(c, DIT_ESHAPE, "bad attention shape");
-  if (flags & ~DIT_ATTN_BOUNDED_LOGITS) return fail(c, DIT_EINVAL, "bad attention flags");
-  if (ldq < heads * 128 || ldk < heads * 128 || ldv < heads * 128 || ldo < heads * 128)
-    return fail(c, DIT_ESHAPE, "row stride smaller than heads*128");
-  hipStream_t s = (hipStream_t)hip_stream;
-  HIPCK(dit::launch_transpose_v_bf16(v, ldv, vt_ws, Lk, heads, s));
-  HIPCK(dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt_ws, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads,
-                                    (flags & DIT_ATTN_BOUNDED_LOGITS) != 0, s));
-  HIPCK(hipStreamSynchronize(s));
-  return DIT_OK;
-}
-
 }  // extern "C"
 
-// ------------------------------------------------------- allocation-free attention
-// Transposed values of dit_attention_bf16_noalloc.  In host code `scratch`
-// names a host-side stand-in, not device memory: kernels and copies take
-// the address hipGetSymbolAddress returns for the current device.
+// ------------------------------------------------------- attention alone
+// Device memory of the attention entry points, which allocate nothing:
+// transposed values of dit_attention_bf16_noalloc, and the pieces of shared
+// attention items of both.  In host code these names are host-side
+// stand-ins, not device memory: kernels take the addresses that
+// hipGetSymbolAddress returns for the current device.
 static __device__ __align__(256) uint16_t scratch[DIT_NOALLOC_VT_MAX_ELEMS];
+namespace {
+constexpr int kPieceSlots = 2;                     // calls in flight on one GPU that may share items
+constexpr size_t kPieceBytes = (size_t)66 << 20;   // flash_attn_ws_bytes of 256 CUs (65 MiB)
+}  // namespace
+static __device__ __align__(256) unsigned char pieces[kPieceSlots * kPieceBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
-void* g_scratch_ptr[kMaxDevices] = {};
+struct DeviceScratch {
+  void* vt = nullptr;
+  char* pieces = nullptr;
+  bool used[kPieceSlots] = {};
+} g_scratch[kMaxDevices];
 
-// The current device's copy of `scratch`, looked up once per device.
-dit_status scratch_ptr(void** out) {
+// The current device's copies of the arrays, looked up once per device.
+dit_status device_scratch(DeviceScratch** out) {
   dit_cache* c = nullptr;
   int dev = -1;
   HIPCK(hipGetDevice(&dev));
   if (dev < 0 || dev >= kMaxDevices) return fail(c, DIT_EINVAL, "device index out of range");
   std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (!g_scratch_ptr[dev]) {
-    void* p = nullptr;
-    HIPCK(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-    if (!p) return fail(c, DIT_EHIP, "hipGetSymbolAddress returned no address");
-    g_scratch_ptr[dev] = p;
+  DeviceScratch& d = g_scratch[dev];
+  if (!d.vt) {
+    void *vt = nullptr, *pc = nullptr;
+    HIPCK(hipGetSymbolAddress(&vt, HIP_SYMBOL(scratch)));
+    HIPCK(hipGetSymbolAddress(&pc, HIP_SYMBOL(pieces)));
+    if (!vt || !pc) return fail(c, DIT_EHIP, "hipGetSymbolAddress returned no address");
+    d.pieces = (char*)pc;
+    d.vt = vt;
   }
-  *out = g_scratch_ptr[dev];
+  *out = &d;
   return DIT_OK;
 }
-}  // namespace
 
-extern "C" dit_status dit_attention_bf16_noalloc(const void* q, int64_t ldq, const void* k, int64_t ldk,
-                                                 const void* v, int64_t ldv, void* o, int64_t ldo, int32_t Lq,
-                                                 int32_t Lk, int32_t heads, int32_t flags, void* hip_stream) {
+// A slot of the piece array for the time of one call (the calls return after
+// their stream has drained).  With every slot taken by calls of other threads
+// the launch runs without one: whole query blocks only, the same result up
+// to the rounding of the sums.
+struct PieceSlot {
+  DeviceScratch* d;
+  int slot = -1;
+  PieceSlot(DeviceScratch* d_, size_t bytes) : d(d_) {
+    if (bytes == 0 || bytes > kPieceBytes) return;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    for (int i = 0; i < kPieceSlots && slot < 0; ++i)
+      if (!d->used[i]) {
+        d->used[i] = true;
+        slot = i;
+      }
+  }
+  ~PieceSlot() {
+    if (slot < 0) return;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    d->used[slot] = false;
+  }
+  PieceSlot(const PieceSlot&) = delete;
+  PieceSlot& operator=(const PieceSlot&) = delete;
+  float* get() const { return slot < 0 ? nullptr : (float*)(d->pieces + slot * kPieceBytes); }
+};
+
+dit_status attention_call(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v, int64_t ldv, void* o,
+                          int64_t ldo, int Lq, int Lk, int heads, int flags, void* vt, DeviceScratch* d,
+                          hipStream_t s) {
+  dit_cache* c = nullptr;
+  int dev = 0, ncu = 256;
+  hipGetDevice(&dev);
+  hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  const PieceSlot ws(d, dit::flash_attn_ws_bytes(Lq, Lk, heads, 1, ncu));
+  hipError_t e = dit::launch_transpose_v_bf16(v, ldv, vt, Lk, heads, s);
+  if (e == hipSuccess)
+    e = dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads,
+                                    (flags & DIT_ATTN_BOUNDED_LOGITS) != 0, s, ncu, ws.get());
+  const hipError_t done = hipStreamSynchronize(s);  // the slot is free only after it
+  HIPCK(e);
+  HIPCK(done);
+  return DIT_OK;
+}
+
+dit_status check_attention(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v, int64_t ldv,
+                           const void* o, int64_t ldo, int32_t Lq, int32_t Lk, int32_t heads, int32_t flags) {
   dit_cache* c = nullptr;
   if (!q || !k || !v || !o) return fail(c, DIT_EINVAL, "null argument");
   if (Lq < 1 || Lk < 1 || heads < 1) return fail(c, DIT_ESHAPE, "bad attention shape");
   if (flags & ~DIT_ATTN_BOUNDED_LOGITS) return fail(c, DIT_EINVAL, "bad attention flags");
   if (ldq < heads * 128 || ldk < heads * 128 || ldv < heads * 128 || ldo < heads * 128)
     return fail(c, DIT_ESHAPE, "row stride smaller than heads*128");
+  return DIT_OK;
+}
+}  // namespace
+
+extern "C" dit_status dit_attention_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v,
+                                         int64_t ldv, void* o, int64_t ldo, int32_t Lq, int32_t Lk, int32_t heads,
+                                         int32_t flags, void* vt_ws, void* hip_stream) {
+  if (!vt_ws) return fail(nullptr, DIT_EINVAL, "null argument");
+  TRY(check_attention(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, flags));
+  DeviceScratch* d = nullptr;
+  TRY(device_scratch(&d));
+  return attention_call(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, flags, vt_ws, d, (hipStream_t)hip_stream);
+}
+
+extern "C" dit_status dit_attention_bf16_noalloc(const void* q, int64_t ldq, const void* k, int64_t ldk,
+                                                 const void* v, int64_t ldv, void* o, int64_t ldo, int32_t Lq,
+                                                 int32_t Lk, int32_t heads, int32_t flags, void* hip_stream) {
+  TRY(check_attention(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, flags));
   const size_t need = (size_t)heads * 128 * rup((size_t)Lk, 64);
   if (need > (size_t)DIT_NOALLOC_VT_MAX_ELEMS)
-    return fail(c, DIT_ESHAPE, "heads * 128 * round_up(Lk, 64) = " + std::to_string(need) +
-                                   " exceeds the allocation-free limit of " +
-                                   std::to_string((size_t)DIT_NOALLOC_VT_MAX_ELEMS) + " elements");
-  void* vt = nullptr;
-  TRY(scratch_ptr(&vt));
-  hipStream_t s = (hipStream_t)hip_stream;
-  HIPCK(dit::launch_transpose_v_bf16(v, ldv, vt, Lk, heads, s));
-  HIPCK(dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads,
-                                    (flags & DIT_ATTN_BOUNDED_LOGITS) != 0, s));
-  HIPCK(hipStreamSynchronize(s));
-  return DIT_OK;
+    return fail(nullptr, DIT_ESHAPE, "heads * 128 * round_up(Lk, 64) = " + std::to_string(need) +
+                                         " exceeds the allocation-free limit of " +
+                                         std::to_string((size_t)DIT_NOALLOC_VT_MAX_ELEMS) + " elements");
+  DeviceScratch* d = nullptr;
+  TRY(device_scratch(&d));
+  return attention_call(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, flags, d->vt, d, (hipStream_t)hip_stream);
 }

@@ -675,10 +675,10 @@ __device__ __forceinline__ void barrier_no_fence() { asm volatile("s_barrier" ::
 // Transposed values straight from the accumulators of a wave that owns 64
 // rows x one 128-column head group (4 x 8 blocks of 16 x 16).  In a block,
 // lane (lr, lq) holds column lr and rows 4 lq .. 4 lq + 3; with the key order
-// of the transposed layout (slot 8 ((k >> 2) & 1) + 4 (k >> 3) + (k & 3)
-// inside each 16-key group) these are the four consecutive slots from
-// 8 (lq & 1) + 4 (lq >> 1), one 8-byte store.  The host admits this only for
-// 32-row aligned segments (a pair of blocks is one sequence's keys kb ..
+// of the transposed layout (slot 8 ((k >> 2) & 3) + 4 (k >> 4) + (k & 3)
+// inside each 32-key group) those of a pair of blocks are the eight
+// consecutive slots from 8 lq, one 16-byte store.  The host admits this only
+// for 32-row aligned segments (a pair of blocks is one sequence's keys kb ..
 // kb + 31, kb a multiple of 32), or for one sequence in one piece, whose last
 // pair may end past its last key inside the padded key range.
 __device__ __forceinline__ void store_vt(const Prob& P, const f32x4_t (&acc)[4][8], int m_base, int ncol0,
@@ -700,16 +700,15 @@ __device__ __forceinline__ void store_vt(const Prob& P, const f32x4_t (&acc)[4][
       z = mm / P.vt_rows1;
       key = P.vt_key1 + mm % P.vt_rows1;
     }
-    bf16_t* base = P.vt + ((int64_t)(z * P.vt_heads + h) * 128 + lr) * P.vt_ld + key + 8 * (lq & 1) + 4 * (lq >> 1);
+    bf16_t* base = P.vt + ((int64_t)(z * P.vt_heads + h) * 128 + lr) * P.vt_ld + key + 8 * lq;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const f32x4_t& a = acc[2 * i + e][j];
-        const float b = bias[j];
-        *(uint2*)(base + (int64_t)(16 * j) * P.vt_ld + 16 * e) =
-            make_uint2(pack_bf16x2(a[0] + b, a[1] + b), pack_bf16x2(a[2] + b, a[3] + b));
-      }
+    for (int j = 0; j < 8; ++j) {
+      const f32x4_t &a = acc[2 * i][j], &c = acc[2 * i + 1][j];
+      const float b = bias[j];
+      *(uint4*)(base + (int64_t)(16 * j) * P.vt_ld) =
+          make_uint4(pack_bf16x2(a[0] + b, a[1] + b), pack_bf16x2(a[2] + b, a[3] + b),
+                     pack_bf16x2(c[0] + b, c[1] + b), pack_bf16x2(c[2] + b, c[3] + b));
+    }
   }
 }
 // 256 x 256 tiles, 8 waves of 64 x 128, BK = 64, with the whole 160 KB of

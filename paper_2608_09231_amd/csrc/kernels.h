@@ -28,7 +28,7 @@ struct GemmArgs {
   // [vt_col0, vt_col0 + 128 vt_heads) are not stored in C but written, with
   // bias and bf16 rounding as usual, as vt[z][head][d][key] with row stride
   // vt_ld and the key order of launch_transpose_v_bf16 (permuted inside
-  // 16-key groups).  Output row m (m < vt_split: segment 0, else segment 1
+  // 32-key groups).  Output row m (m < vt_split: segment 0, else segment 1
   // with m - vt_split) of a segment with R rows per sequence and key offset
   // k0 goes to sequence m / R, key k0 + m % R.
   void* vt = nullptr;
@@ -65,9 +65,13 @@ hipError_t launch_transpose_v_bf16(const void* v, int64_t ldv, void* vt, int Lk,
                                    int64_t zs = 0, int64_t gz = 0);
 hipError_t launch_flash_attn_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk,
                                   const void* vt, int ldvt, void* o, int64_t ldo, int Lq,
-                                  int Lk, int heads, bool bounded_logits, hipStream_t s,
+                                  int Lk, int heads, bool bounded_logits, hipStream_t s, int n_cu, float* ws,
                                   int split = 0x7fffffff, int64_t gap = 0, int nseq = 1, int64_t zs = 0,
                                   int64_t gz = 0);
+// Bytes of the workspace ws with which launch_flash_attn_bf16 shares the key
+// ranges of its last round out (0: it would not); without it (nullptr) every
+// work-group takes whole query blocks.
+size_t flash_attn_ws_bytes(int Lq, int Lk, int heads, int nseq, int n_cu);
 // f32 attention, head_dim <= 128 (multiple of 4).
 hipError_t launch_attn_f32(const float* q, int64_t ldq, const float* k, int64_t ldk,
                            const float* v, int64_t ldv, float* o, int64_t ldo, int Lq, int Lk,

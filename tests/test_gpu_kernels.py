@@ -246,3 +246,64 @@ def test_attention_bounded_logits_rms_normalised(L, heads):
     rows = np.sort(RNG.choice(L, min(L, 64), replace=False))
     ref = round_bf16(dit.attention(q[rows], k, v, heads, 128))
     assert rel_l2(got[rows], ref) < 4e-3
+
+
+def bounded_case(torch, Lq, Lk, heads, bounded):
+    H = heads * 128
+
+    def mk(n, norm):
+        x = RNG.standard_normal((n, H)) * 2.0
+        b = bf16_bits(dit.rms_heads(x, heads, 128) if norm else x)
+        return b, bits_to_f64(b)
+    (q_b, q), (k_b, k), (v_b, v) = mk(Lq, bounded), mk(Lk, bounded), mk(Lk, False)
+    args = dict(Lq=Lq, Lk=Lk, heads=heads, ldq=H, ldk=H, ldv=H, ldo=H,
+                flags=binding.ATTN_BOUNDED_LOGITS if bounded else 0)
+    rows = np.unique(np.concatenate([[0, Lq - 1], RNG.choice(Lq, min(Lq, 40), replace=False)]))
+    ref = round_bf16(dit.attention(q[rows], k, v, heads, 128))
+    return [dev(torch, t) for t in (q_b, k_b, v_b)], args, rows, ref
+
+
+@pytest.mark.parametrize("bounded", [True, False])
+@pytest.mark.parametrize("Lq,Lk,heads", [
+    (1, 64 * 9, 1),       # one item, shared in two
+    (257, 4100, 3),       # a ragged second query block, shares of one XCD in several pieces
+    (8300, 700, 8),       # 33 items an XCD: a whole round and one shared item
+    (8192, 130, 10),      # 40 an XCD, three tiles: whole items in the last round
+    (2048, 2050, 1),      # eight items, a last tile of two keys
+])
+def test_attention_last_round(Lq, Lk, heads, bounded):
+    """Items per work-group, the shared last round and its pieces, ragged
+    queries and keys: sampled rows against float64."""
+    torch = torch_cuda()
+    (q, k, v), args, rows, ref = bounded_case(torch, Lq, Lk, heads, bounded)
+    o = torch.full((Lq, heads * 128), 0x7fc0, dtype=torch.int16, device="cuda")  # NaN: every row written
+    ws = torch.zeros(heads * 128 * ((Lk + 63) // 64 * 64), dtype=torch.int16, device="cuda")
+    binding.attention_bf16(q, k, v, o, vt_ws=ws, **args)
+    got = host_bf16(o)
+    assert np.all(np.isfinite(got))
+    assert rel_l2(got[rows], ref) < 4e-3
+
+
+def test_attention_calls_in_flight():
+    """Four threads with streams of their own: two calls hold the shared
+    items' memory, further ones run unshared; all within the same bar."""
+    import threading
+    torch = torch_cuda()
+    cases, errs = [bounded_case(torch, 600, 3000, 2, True) for _ in range(4)], []
+
+    def work(case):
+        try:
+            (q, k, v), args, rows, ref = case
+            s = torch.cuda.Stream()
+            o = torch.zeros((600, 256), dtype=torch.int16, device="cuda")
+            ws = torch.zeros(256 * 3008, dtype=torch.int16, device="cuda")
+            torch.cuda.synchronize()
+            for _ in range(20):
+                binding.attention_bf16(q, k, v, o, vt_ws=ws, stream=s, **args)
+                assert rel_l2(host_bf16(o)[rows], ref) < 4e-3
+        except Exception as e:  # reported by the main thread
+            errs.append(e)
+    ts = [threading.Thread(target=work, args=(c,)) for c in cases]
+    [t.start() for t in ts]
+    [t.join() for t in ts]
+    assert not errs, errs
