@@ -267,11 +267,7 @@ dit_status gemm(dit_cache* c, GemmArgs* g, int n, int cls) {
   if (c->bf16) {
     HIPCK(dit::launch_gemm_bf16(g, n, c->stream, c->n_cu));
   } else {
-    HIPCK(dit::launch_gemm_f32(g, n, c->stream));
-    for (int i = 0; i < n; ++i)
-      if (g[i].rms_cols > 0)
-        HIPCK(dit::launch_rms_heads_f32((float*)g[i].C, g[i].ldc, g[i].M, g[i].rms_cols,
-                                        c->cfg.head_dim, c->stream));
+    HIPCK(dit::launch_gemm_f32(g, n, c->cfg.head_dim, c->n_cu, c->stream));  // with the per-head norm
   }
   return DIT_OK;
 }
@@ -984,7 +980,9 @@ dit_status final_project(dit_cache* c, int b, int cls, float* latent = nullptr, 
   if (c->bf16) {
     HIPCK(dit::launch_gemm_bf16(&g, 1, c->stream, c->n_cu));
   } else {
-    HIPCK(dit::launch_gemm_f32(&g, 1, c->stream));
+    g.euler_x = latent;  // f32: the Euler update in the epilogue
+    g.euler_alpha = dsig;
+    HIPCK(dit::launch_gemm_f32(&g, 1, c->cfg.head_dim, c->n_cu, c->stream));
   }
   return DIT_OK;
 }
@@ -1184,7 +1182,7 @@ dit_status run_batch(dit_cache* c, int S, float* latents, const void* text_emb, 
   const bool step = !sstream && c->bf16 && dit::step_fused_fits(C, H, nb);
   const bool spec_path = sstream || step;
   const bool fused = !spec_path && c->bf16 && dit::reuse_fused_fits(C, H);
-  const bool fused_euler = !pair && proj_fits(c) && !unipc;  // Euler folded into the projection
+  const bool fused_euler = !pair && (!c->bf16 || proj_fits(c)) && !unipc;  // Euler folded into the projection
   const double thr = std::log(p.tau / (1.0 - p.tau));
   // mu(B, T) of the static policy: computed steps at floor(i T / B)
   std::vector<uint8_t> mu(T, 0);
@@ -1279,13 +1277,14 @@ dit_status run_batch(dit_cache* c, int S, float* latents, const void* text_emb, 
                                           sh0, sc0, t ? c->partials : nullptr, sums, nullptr, c->stream));
       } else {
         Scope sc(c, DIT_K_INDICATOR, (double)NH * c->esz * (t == 0 ? 2 : (l.i_prev == l.i_last ? 3 : 4)));
-        TRY(typed(c, [&](auto* tp) {
-          using Ty = std::remove_pointer_t<decltype(tp)>;
-          return dit::launch_cast_from_f32<Ty>(lat(j), (Ty*)c->xs, (int64_t)NC, c->stream);
-        }));
-        GemmArgs g = lin_args(c, c->xs, C, c->M.img_in, l.h, H, N);
-        if (c->bf16) { HIPCK(dit::launch_gemm_bf16(&g, 1, c->stream, c->n_cu)); }
-        else { HIPCK(dit::launch_gemm_f32(&g, 1, c->stream)); }
+        GemmArgs g = lin_args(c, lat(j), C, c->M.img_in, l.h, H, N);
+        if (c->bf16) {
+          HIPCK(dit::launch_cast_from_f32<bf16_t>(lat(j), (bf16_t*)c->xs, (int64_t)NC, c->stream));
+          g.A = c->xs;
+          HIPCK(dit::launch_gemm_bf16(&g, 1, c->stream, c->n_cu));
+        } else {  // the latent is stored in S already
+          HIPCK(dit::launch_gemm_f32(&g, 1, c->cfg.head_dim, c->n_cu, c->stream));
+        }
         TRY(typed(c, [&](auto* tp) {
           using Ty = std::remove_pointer_t<decltype(tp)>;
           return dit::launch_indicator<Ty>((const Ty*)l.h, (Ty*)l.mbuf[l.i_new], (const Ty*)mp, (const Ty*)ml, N,

@@ -24,6 +24,10 @@ struct GemmArgs {
   // gate + (m / gseg) * gstride.  gseg = 0: one vector; else a multiple of 32.
   int gseg = 0;
   int64_t gstride = 0;
+  // f32 only: the result goes into the Euler update euler_x[m][n] +=
+  // euler_alpha (acc + bias) (row stride ldc) instead of C.
+  float* euler_x = nullptr;
+  float euler_alpha = 0.f;
   // Values transposed for attention (vt != nullptr): output columns
   // [vt_col0, vt_col0 + 128 vt_heads) are not stored in C but written, with
   // bias and bf16 rounding as usual, as vt[z][head][d][key] with row stride
@@ -51,7 +55,7 @@ hipError_t launch_proj_small_n(const void* A, int64_t lda, const void* W, int64_
                                float* out, int64_t ldo, float* x, int64_t ldx, float alpha, int M, int N,
                                int K, hipStream_t s);
 // f32 GEMM (small f32 workloads); bias f32; rms_cols handled by rms_heads_f32.
-hipError_t launch_gemm_f32(const GemmArgs* g, int n, hipStream_t s);
+hipError_t launch_gemm_f32(const GemmArgs* g, int n, int head_dim, int n_cu, hipStream_t s);
 
 // Flash attention, bf16, head_dim 128. vt = v transposed per head:
 // [heads][128][ldvt], ldvt = round_up(Lk, 64), zero padded.  Rows r >= split

@@ -82,6 +82,24 @@ def test_small_f32_parity():
     parity("small_f32")
 
 
+@pytest.mark.parametrize("heads,hd,F,C,ctx,N,Nt", [
+    (4, 16, 37, 5, 21, 33, 7),        # odd widths: no 16-byte rows; heads of half a tile
+    (1, 64, 256, 16, 64, 15, 2),      # less than one 16-row tile; heads wider than the tile
+    (2, 128, 300, 12, 50, 260, 21),   # 128-wide heads
+    (8, 64, 512, 16, 64, 1100, 52),   # 64 x 64 tiles, heads of one tile
+    (32, 16, 500, 16, 64, 1100, 52),  # 64 x 64 tiles, four heads a tile
+])
+def test_f32_layer_shapes(monkeypatch, heads, hd, F, C, ctx, N, Nt):
+    """The f32 GEMM's tile sizes, shared K, unaligned rows and fused norm, and
+    the f32 attention's head widths and ragged key blocks, through one double
+    and one single block."""
+    cfg = synth.ModelConfig(name="case", dtype="f32", n_double=1, n_single=1, n_cross=0, hidden=heads * hd,
+                            heads=heads, head_dim=hd, mlp_hidden=F, in_channels=C, ctx_dim=ctx, n_img=N, n_txt=Nt)
+    monkeypatch.setitem(synth.WORKLOADS, "case",
+                        synth.Workload("case", cfg, T=4, B=2, shift=3.0, guidance=1.0, seed=31))
+    parity("case")
+
+
 def test_small_bf16_parity():
     sched, ores, err = parity("small_bf16")
     print("small_bf16 rel-L2", err, "schedule", sched.full.tolist())
