@@ -103,6 +103,7 @@ struct dit_cache {
   // sample that computes) runs the block stack together, stream-major rows
   // [txt_0; ...; txt_{Q-1}; img_0; ...; img_{Q-1}] (see full_stack_multi)
   bool stacked = false;
+  bool several = false;  // the running call advances several samples
 
   void* wdev = nullptr;
   size_t wbytes = 0;
@@ -257,6 +258,7 @@ GemmArgs lin_args(const dit_cache* c, const void* A, int64_t lda, const Lin& l, 
   g.A = A; g.lda = lda; g.W = l.w; g.ldw = l.in; g.bias = l.b;
   g.C = C; g.ldc = ldc; g.gate = nullptr;
   g.M = M; g.N = l.out; g.K = l.in; g.flags = flags;
+  g.one_chain = c->several;
   return g;
 }
 
@@ -1170,7 +1172,9 @@ dit_status run_batch(dit_cache* c, int S, float* latents, const void* text_emb, 
   }
   TRY(ensure_lanes(c, S));
   TRY(ensure_T(c, T, S));
+  c->several = false;  // what is formed once per sample has the same shapes for any S
   TRY(prepare(c, S, text_emb, sig, T));
+  c->several = S > 1;
 
   const bool pair = nb == 2;
   const bool unipc = p.solver == DIT_SOLVER_UNIPC;

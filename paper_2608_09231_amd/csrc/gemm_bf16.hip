@@ -874,7 +874,143 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(Batch b) {
   epi.slab_pass16(acc[2], acc[3], 1, old[1], lr, lq);
 }
 
-typedef __bf16 bf16x8v_t __attribute__((ext_vector_type(8)));
+// Few rows or few tiles: 32 x NT outputs per work-group, operands straight
+// from global memory into the fragments of 16x16x32 MFMAs, K shared by the
+// eight waves (NT = 128: by four, the other four take the second 64 columns).
+// What bounds it is latency (small models) or the weights' bytes (a few rows
+// against a large table), not the matrix cores: many loads in flight from many
+// work-groups count, and an LDS pipeline with one slice in flight per
+// work-group has neither.  Through the entry point (11 us of it launch and
+// wait), against 32 x 256 tiles: 28 x 3072 x 3072 51.6 -> 30.4 us, 240 x 256 x 1280
+// 32.7 -> 21.6 us, 240 x 768 x 256 with the norm 23.7 -> 17.9 us.  Three steps'
+// loads in flight at 122 registers (two work-groups per CU) beat four at 146.
+// Requires K % 8 == 0 and the LDS-staged epilogue's conditions.
+template <int NT>
+__global__ __launch_bounds__(512, 4) void gemm_bf16_small_kernel(Batch b) {
+  constexpr int NH = NT / 64, KS = 8 / NH;  // column halves, waves that share K
+  constexpr int LD = 68;                    // floats per staged row of 64
+  __shared__ __attribute__((aligned(16))) float part[8][32][LD];
+
+  if ((int)blockIdx.x >= b.total) return;
+  int lt = xcd_remap(blockIdx.x, b.total);
+  const bool second = lt >= b.tiles0;
+  Prob P = second ? b.p1 : b.p0;
+  if (second) lt -= b.tiles0;
+  const int m0 = lt % P.tiles_m * 32, n0 = lt / P.tiles_m * NT;  // neighbours share the weights
+  if (P.gseg > 0) P.gate += (int64_t)(m0 / P.gseg) * P.gstride;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lq = lane >> 4;
+  const int ks = wave % KS, nh = wave / KS;
+  const bf16_t *ap[2], *wp[4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) ap[i] = P.A + (int64_t)min(m0 + 16 * i + lr, P.M - 1) * P.lda;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) wp[j] = P.W + (int64_t)min(n0 + 64 * nh + 16 * j + lr, P.N - 1) * P.ldw;
+  const int steps = (P.K + 31) / 32, per = (steps + KS - 1) / KS;
+  const int s0 = ks * per, s1 = min(steps, s0 + per);
+  f32x4_t acc[2][4] = {};
+  auto load8 = [&](const bf16_t* p, int k) {
+    const uint4 v = *(const uint4*)(p + min(k, P.K - 8));
+    return __builtin_bit_cast(bf16x8_t, k < P.K ? v : make_uint4(0, 0, 0, 0));
+  };
+  constexpr int U = 3;  // steps whose loads are in flight together
+  for (int s = s0; s < s1; s += U) {
+    bf16x8_t a[U][2], w[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s + u >= s1) break;
+      const int k = 32 * (s + u) + 8 * lq;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w[u][j] = load8(wp[j], k);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) a[u][i] = load8(ap[i], k);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s + u >= s1) break;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][i], w[u][j], acc[i][j], 0, 0, 0);
+    }
+  }
+  // acc[i][j][r] = C[16 i + 4 lq + r][16 j + lr] of the wave's 32 x 64
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[wave][16 * i + 4 * lq + r][16 * j + lr] = acc[i][j][r];
+  __syncthreads();
+
+  // 16 threads per row: columns 4 c .. + 3 of each half, added in wave order
+  const int row = tid >> 4, c = tid & 15, m = m0 + row;
+  float v[NH][4];
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    const int n = n0 + 64 * h + 4 * c;
+    f32x4_t t = {};
+#pragma unroll
+    for (int w = 0; w < KS; ++w) t += *(const f32x4_t*)&part[KS * h + w][row][4 * c];
+    uint2 bb = make_uint2(0, 0);
+    if (P.bias && n < P.N) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const uint32_t x = P.bias[n + 2 * e] | ((uint32_t)P.bias[n + 2 * e + 1] << 16);
+        if (e) bb.y = x; else bb.x = x;
+      }
+    }
+    v[h][0] = t[0] + __uint_as_float(bb.x << 16); v[h][1] = t[1] + __uint_as_float(bb.x & 0xffff0000u);
+    v[h][2] = t[2] + __uint_as_float(bb.y << 16); v[h][3] = t[3] + __uint_as_float(bb.y & 0xffff0000u);
+  }
+  if constexpr (NT == 128) {
+    if (n0 < P.rms_cols) {  // one 128-wide head per tile
+      float ss = 0.f;
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ss += v[h][e] * v[h][e];
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o, 64);
+      const float sc = rsqrtf(ss * (1.f / 128.f) + DIT_RMS_EPS);
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[h][e] *= sc;
+    }
+  }
+  if (m >= P.M) return;
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    const int n = n0 + 64 * h + 4 * c;
+    if (n >= P.N) continue;
+    if (n >= P.gelu_from)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[h][e] = gelu_tanh_f(v[h][e]);
+    if (P.flags & DIT_EPI_SILU)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[h][e] = silu_f(v[h][e]);
+    const int64_t at = (int64_t)m * P.ldc + n + (n >= P.gap_at ? P.gap : 0);
+    if (P.flags & DIT_EPI_F32) {
+      *(float4*)((float*)P.C + at) = make_float4(v[h][0], v[h][1], v[h][2], v[h][3]);
+      continue;
+    }
+    uint2* o = (uint2*)((bf16_t*)P.C + at);
+    if (P.flags & DIT_EPI_GATED_RES) {
+      const uint2 x = *o;
+      const float4 g = *(const float4*)(P.gate + n);
+      v[h][0] = __uint_as_float(x.x << 16) + g.x * v[h][0];
+      v[h][1] = __uint_as_float(x.x & 0xffff0000u) + g.y * v[h][1];
+      v[h][2] = __uint_as_float(x.y << 16) + g.z * v[h][2];
+      v[h][3] = __uint_as_float(x.y & 0xffff0000u) + g.w * v[h][3];
+    }
+    *o = make_uint2(pack_bf16x2(v[h][0], v[h][1]), pack_bf16x2(v[h][2], v[h][3]));
+  }
+}
+
 
 // Small-N projection (the final layer, N = C <= 128): v[m][c] = sum_k A[m][k] W[c][k]
 // + bias[c], or with x != nullptr the Euler update x[m][c] += alpha * v[m][c]
@@ -935,7 +1071,10 @@ struct Cfg {
 
 // eff: relative MFMA efficiency of a full tile (measured ordering); the
 // chooser minimises rounds x per-round work / eff over the configs a
-// problem admits.
+// problem admits.  The 32 x 128 tiles keep three slices in flight and two
+// work-groups per CU, for few rows against many weights: 28 x 52224 x 3072
+// 89.5 -> 72.4 us (32 x 256 tiles, one slice in flight), 512 x 3072 x 4096 60.7 ->
+// 48.2 us; in two rounds they lose (256 x 9216 x 3072: 90 against 71 us).
 #define DIT_DMA_CFG(BM, BN, WGM, WGN, BK_, ST, WPC, EFF)                                      \
   {BM, BN, BN / WGN, WPC, 64 * WGM * WGN, BK_,                                                 \
    kLdsEpilogue<BN / WGN, WGM * WGN, ST * (BM + BN) * BK_ * 2>, EFF, true,                     \
@@ -946,12 +1085,16 @@ const Cfg kCfgs[] = {
     DIT_DMA_CFG(256, 128, 4, 1, 64, 2, 1, 0.72f),
     DIT_DMA_CFG(128, 128, 4, 1, 64, 2, 2, 0.85f),
     DIT_DMA_CFG(32, 256, 1, 4, 64, 2, 2, 0.45f),
+    DIT_DMA_CFG(32, 128, 1, 4, 64, 4, 2, 0.44f),
     {256, 128, 128, 1, 256, 64, false, 0.60f, false, gemm_bf16_kernel<256, 128, 4, 1>, 0},
     {128, 128, 128, 2, 256, 64, false, 0.55f, false, gemm_bf16_kernel<128, 128, 4, 1>, 0},
     {32, 256, 64, 2, 256, 64, false, 0.30f, false, gemm_bf16_kernel<32, 256, 1, 4>, 0},
+    // picked by their own rule: plain layers, and those with the per-head norm
+    {32, 64, 64, 1, 512, 8, true, 0.f, false, gemm_bf16_small_kernel<64>, 0},
+    {32, 128, 128, 1, 512, 8, true, 0.f, false, gemm_bf16_small_kernel<128>, 0},
 };
 #undef DIT_DMA_CFG
-constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
+constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]), kSmallCfg = kNumCfgs - 2;
 
 Prob make_prob(const GemmArgs& g, int bm, int bn) {
   Prob p;
@@ -999,19 +1142,33 @@ int pick_cfg(const GemmArgs* g, int n, int n_cu) {
       if (g[i].K % k.bk || g[i].K < k.min_k) return false;
     return true;
   };
-  bool shallow = true;  // K <= 256: the tile writes dominate, more workgroups stream better
+  auto tiles_of = [&](int bm, int bn) {
+    long t = 0;
+    for (int i = 0; i < n; ++i) t += (long)((g[i].M + bm - 1) / bm) * ((g[i].N + bn - 1) / bn);
+    return t;
+  };
+  // Few tiles: at most one 32 x 64 (with the norm 32 x 128) tile per CU.  Through
+  // the entry point, small kernel against 32 x 128 tiles with four slices in
+  // LDS: 48 tiles, K = 3072 30 / 39 us; 81, K = 1920 25 / 30; 192, K = 256 16 / 18;
+  // the line is crossed between 288 (K = 3072: 54 / 52) and 512 (K = 1024: 26 / 24).
+  {
+    const int c = kSmallCfg + (rms ? 1 : 0);
+    bool one_chain = false;
+    for (int i = 0; i < n; ++i) one_chain |= g[i].one_chain;
+    if (epi_ok && !one_chain && tiles_of(kCfgs[c].bm, kCfgs[c].bn) <= n_cu) return c;
+  }
+  // K <= 256: the tile writes dominate, more workgroups stream better
+  bool shallow = tiles_of(128, 128) >= n_cu;
   for (int i = 0; i < n; ++i) shallow &= g[i].K <= 256 && g[i].M >= 512;
   if (shallow)
-    for (int c = 0; c < kNumCfgs; ++c)
+    for (int c = 0; c < kSmallCfg; ++c)
       if (kCfgs[c].bm == 128 && kCfgs[c].bn == 128 && admits(kCfgs[c])) return c;
   int best = -1;
   double best_t = 1e300;
-  for (int c = 0; c < kNumCfgs; ++c) {
+  for (int c = 0; c < kSmallCfg; ++c) {
     const Cfg& k = kCfgs[c];
     if (!admits(k)) continue;
-    long tiles = 0;
-    for (int i = 0; i < n; ++i)
-      tiles += (long)((g[i].M + k.bm - 1) / k.bm) * ((g[i].N + k.bn - 1) / k.bn);
+    const long tiles = tiles_of(k.bm, k.bn);
     const long slots = (long)n_cu * k.wg_per_cu;
     const long rounds = (tiles + slots - 1) / slots;
     const double t = (double)rounds * k.bm * k.bn * k.wg_per_cu / k.eff;

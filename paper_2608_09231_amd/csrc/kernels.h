@@ -24,6 +24,10 @@ struct GemmArgs {
   // gate + (m / gseg) * gstride.  gseg = 0: one vector; else a multiple of 32.
   int gseg = 0;
   int64_t gstride = 0;
+  // Every output's products are added in one chain over K whatever the number
+  // of rows (bf16): the stacked launches of several samples then give a
+  // sample the same bits however many share the launch.
+  bool one_chain = false;
   // f32 only: the result goes into the Euler update euler_x[m][n] +=
   // euler_alpha (acc + bias) (row stride ldc) instead of C.
   float* euler_x = nullptr;

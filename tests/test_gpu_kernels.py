@@ -145,6 +145,37 @@ def test_gemm_ring_shortest_pipelines(K, flags):
     assert_bf16_close(host_bf16(out), round_bf16(c0 + g.astype(np.float64) * y if gated else y))
 
 
+@pytest.mark.parametrize("flags", [binding.EPI_STORE, binding.EPI_F32, binding.EPI_GATED_RES, binding.EPI_SILU])
+@pytest.mark.parametrize("M,N,K", [
+    (33, 392, 40),      # small kernel: a ragged second row tile, less than one step for some waves
+    (5, 1000, 3072),    # the same, all K shared out, a ragged last column tile
+    (31, 16392, 128),   # 32 x 128 tiles: fewer slices than the pipeline holds
+    (100, 16392, 448),  # the same, past the pipeline's depth
+])
+def test_gemm_few_rows(M, N, K, flags):
+    """The kernels for few rows and few tiles, every epilogue, against float64."""
+    torch = torch_cuda()
+    a_b, a = make((M, K))
+    w_b, w = make((N, K), 0.05)
+    b_b, b = make((N,), 0.1)
+    y = a @ w.T + b
+    args = dict(M=M, N=N, K=K, flags=flags)
+    if flags == binding.EPI_F32:
+        out = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+        binding.gemm_bf16(dev(torch, a_b), dev(torch, w_b), dev(torch, b_b), out, **args)
+        np.testing.assert_allclose(out.cpu().numpy(), y, rtol=1e-5, atol=2e-5)
+        return
+    c0_b, c0 = make((M, N))
+    g = RNG.standard_normal(N).astype(np.float32)
+    out, gate = dev(torch, c0_b), None
+    if flags == binding.EPI_GATED_RES:
+        y, gate = c0 + g.astype(np.float64) * y, dev(torch, g)
+    elif flags == binding.EPI_SILU:
+        y = dit.silu(y)
+    binding.gemm_bf16(dev(torch, a_b), dev(torch, w_b), dev(torch, b_b), out, gate=gate, **args)
+    assert_bf16_close(host_bf16(out), round_bf16(y))
+
+
 def test_gemm_ring_rms_gelu_gap_ragged():
     """The ring kernel's store epilogue with the single-block projection's
     column roles at a ragged M: per-head RMS on the first 2 H columns, GELU
