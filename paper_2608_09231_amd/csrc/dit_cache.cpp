@@ -119,7 +119,10 @@ struct dit_cache {
   void* Y = nullptr;       // [cap_seq L, 4H+F]: q | k | v | attn out | mlp hidden
   void* vt = nullptr;      // bf16 [cap_seq, heads, 128, round_up(L, 64)]
   float* modq = nullptr;   // f32 [cap_seq, n_mod]: gathered modulation vectors of one step
-  float* attn_ws = nullptr;  // pieces of shared attention items (flash_attn_ws_bytes), or nullptr
+  // f32 pieces of work shared out in a launch's last round (flash_attn_ws_bytes,
+  // gemm_bf16_ws_bytes), or nullptr: one launch at a time on the stream
+  float* pieces = nullptr;
+  size_t pieces_bytes = 0;
   void* yf = nullptr;      // [N, H] final-layer input
   float* vel = nullptr;    // f32 [nb, N, C]
   float* ones = nullptr;   // f32 [H] (ungated residual)
@@ -267,7 +270,7 @@ dit_status gemm(dit_cache* c, GemmArgs* g, int n, int cls) {
   for (int i = 0; i < n; ++i) flops += 2.0 * g[i].M * (double)g[i].N * g[i].K;
   Scope sc(c, cls, flops);
   if (c->bf16) {
-    HIPCK(dit::launch_gemm_bf16(g, n, c->stream, c->n_cu));
+    HIPCK(dit::launch_gemm_bf16(g, n, c->stream, c->n_cu, c->pieces));
   } else {
     HIPCK(dit::launch_gemm_f32(g, n, c->cfg.head_dim, c->n_cu, c->stream));  // with the per-head norm
   }
@@ -294,7 +297,7 @@ dit_status ln_mod(dit_cache* c, const void* x, int64_t ldx, void* out, int64_t l
 
 // attention over joint rows: q,k,v inside Y (or separate), output into o;
 // nseq stacked sequences in one launch (bf16; see launch_flash_attn_bf16)
-// vt_ready: the projection has already written the transposed values into vt_ws
+// vt_ready: the transposed values are in vt_ws already
 dit_status attention(dit_cache* c, const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v,
                      int64_t ldv, void* o, int64_t ldo, int Lq, int Lk, void* vt_ws, int split = 0x7fffffff,
                      int64_t gap = 0, int nseq = 1, int64_t zs = 0, int64_t gz = 0, bool vt_ready = false) {
@@ -308,7 +311,7 @@ dit_status attention(dit_cache* c, const void* q, int64_t ldq, const void* k, in
     Scope s(c, DIT_K_ATTN, flops);
     // q and k leave the projection through a unit-gain RMS norm: bounded logits
     HIPCK(dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt_ws, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads,
-                                      true, c->stream, c->n_cu, c->attn_ws, split, gap, nseq, zs, gz));
+                                      true, c->stream, c->n_cu, c->pieces, split, gap, nseq, zs, gz));
   } else {
     if (nseq != 1) return fail(c, DIT_EINVAL, "f32 attention runs one sequence per launch");
     Scope s(c, DIT_K_ATTN, flops);
@@ -468,11 +471,20 @@ dit_status ensure_seq(dit_cache* c, int Q) {
     HIPCK(hipMemsetAsync(c->vt, 0, vb, c->stream));
   }
   if (c->stacked && c->cfg.pooled_text) TRY(dalloc(c, &c->modq, (size_t)Q * c->n_mod * 4));
-  if (c->bf16 && !c->attn_ws) {  // one size, whatever the launch; any subset of the sequences may compute
+  if (c->bf16) {  // any subset of the sequences may compute
     const int heads = c->cfg.heads;
     size_t need = c->cfg.n_cross ? dit::flash_attn_ws_bytes(c->N, c->Nt, heads, 1, c->n_cu) : 0;
     for (int n = 1; n <= Q; ++n) need = std::max(need, dit::flash_attn_ws_bytes(c->L, c->L, heads, n, c->n_cu));
-    if (need) TRY(dalloc(c, &c->attn_ws, need));
+    // the widest layer fills the chip with 256 x 256 tiles: some launch may end in a round of few
+    if (rup(LB, 256) / 256 * (rup(std::max(c->F, 3 * c->H), 256) / 256) >= (size_t)c->n_cu)
+      need = std::max(need, dit::gemm_bf16_ws_bytes(c->n_cu));
+    if (need > c->pieces_bytes) {
+      if (c->pieces) hipFree(c->pieces);
+      c->pieces = nullptr;
+      c->pieces_bytes = 0;
+      TRY(dalloc(c, &c->pieces, need));
+      c->pieces_bytes = need;
+    }
   }
   c->cap_seq = Q;
   return DIT_OK;
@@ -706,7 +718,7 @@ dit_status full_stack(dit_cache* c, const Seq& q, int t, int T) {
         g.vt_ld = (int)rup(N, 64);
         g.vt_rows0 = N;
         g.vt_key0 = 0;
-        vt_fused = dit::gemm_bf16_fuses_vt(&g, 1, c->n_cu);
+        vt_fused = dit::gemm_bf16_fuses_vt(&g, 1, c->n_cu, c->pieces != nullptr);
         if (!vt_fused) g.vt = nullptr;
       }
       TRY(gemm(c, &g, 1, cls));
@@ -915,7 +927,7 @@ dit_status full_stack_multi(dit_cache* c, const Seq* seqs, int Q) {
     g[0].rms_cols = g[1].rms_cols = 2 * H;
     with_vt(g[0], N, Nt);   // image rows: keys Nt .. Nt + N - 1 of sequence m / N
     with_vt(g[1], Nt, 0);   // text rows: keys 0 .. Nt - 1 of sequence m / Nt
-    const bool vt_fused = dit::gemm_bf16_fuses_vt(g, 2, c->n_cu);
+    const bool vt_fused = dit::gemm_bf16_fuses_vt(g, 2, c->n_cu, c->pieces != nullptr);
     if (!vt_fused) g[0].vt = g[1].vt = nullptr;
     TRY(gemm(c, g, 2, cls));
     TRY(attn(vt_fused));
@@ -941,7 +953,7 @@ dit_status full_stack_multi(dit_cache* c, const Seq* seqs, int Q) {
     g.gap_at = 3 * H;
     g.gap = H;
     with_vt(g, Nt, 0, Lt, N, Nt);  // the Q text row blocks, then the Q image row blocks
-    const bool vt_fused = dit::gemm_bf16_fuses_vt(&g, 1, c->n_cu);
+    const bool vt_fused = dit::gemm_bf16_fuses_vt(&g, 1, c->n_cu, c->pieces != nullptr);
     if (!vt_fused) g.vt = nullptr;
     TRY(gemm(c, &g, 1, cls));
     TRY(attn(vt_fused));
@@ -980,7 +992,7 @@ dit_status final_project(dit_cache* c, int b, int cls, float* latent = nullptr, 
   }
   GemmArgs g = lin_args(c, c->yf, H, c->M.fin, c->vel + (size_t)b * N * c->C, c->C, N, DIT_EPI_F32);
   if (c->bf16) {
-    HIPCK(dit::launch_gemm_bf16(&g, 1, c->stream, c->n_cu));
+    HIPCK(dit::launch_gemm_bf16(&g, 1, c->stream, c->n_cu, c->pieces));
   } else {
     g.euler_x = latent;  // f32: the Euler update in the epilogue
     g.euler_alpha = dsig;
@@ -1285,7 +1297,7 @@ dit_status run_batch(dit_cache* c, int S, float* latents, const void* text_emb, 
         if (c->bf16) {
           HIPCK(dit::launch_cast_from_f32<bf16_t>(lat(j), (bf16_t*)c->xs, (int64_t)NC, c->stream));
           g.A = c->xs;
-          HIPCK(dit::launch_gemm_bf16(&g, 1, c->stream, c->n_cu));
+          HIPCK(dit::launch_gemm_bf16(&g, 1, c->stream, c->n_cu, c->pieces));
         } else {  // the latent is stored in S already
           HIPCK(dit::launch_gemm_f32(&g, 1, c->cfg.head_dim, c->n_cu, c->stream));
         }
@@ -1506,6 +1518,120 @@ dit_status run_batch(dit_cache* c, int S, float* latents, const void* text_emb, 
 
 }  // namespace
 
+// ------------------------------------------------------- components' scratch
+// Device memory of the component entry points, which allocate nothing:
+// transposed values of dit_attention_bf16_noalloc, and the f32 pieces of work
+// shared out in a launch's last round.  In host code these names are host-side
+// stand-ins, not device memory: kernels take the addresses that
+// hipGetSymbolAddress returns for the current device.
+static __device__ __align__(256) uint16_t scratch[DIT_NOALLOC_VT_MAX_ELEMS];
+namespace {
+constexpr int kPieceSlots = 2;                     // calls in flight on one GPU that may share work out
+constexpr size_t kPieceBytes = (size_t)66 << 20;   // flash_attn_ws_bytes, gemm_bf16_ws_bytes of 256 CUs (65, 64 MiB)
+}  // namespace
+static __device__ __align__(256) unsigned char pieces[kPieceSlots * kPieceBytes];
+
+namespace {
+constexpr int kMaxDevices = 64;
+std::mutex g_scratch_mu;
+struct DeviceScratch {
+  void* vt = nullptr;
+  char* pieces = nullptr;
+  bool used[kPieceSlots] = {};
+} g_scratch[kMaxDevices];
+
+// The current device's copies of the arrays, looked up once per device.
+dit_status device_scratch(DeviceScratch** out) {
+  dit_cache* c = nullptr;
+  int dev = -1;
+  HIPCK(hipGetDevice(&dev));
+  if (dev < 0 || dev >= kMaxDevices) return fail(c, DIT_EINVAL, "device index out of range");
+  std::lock_guard<std::mutex> lock(g_scratch_mu);
+  DeviceScratch& d = g_scratch[dev];
+  if (!d.vt) {
+    void *vt = nullptr, *pc = nullptr;
+    HIPCK(hipGetSymbolAddress(&vt, HIP_SYMBOL(scratch)));
+    HIPCK(hipGetSymbolAddress(&pc, HIP_SYMBOL(pieces)));
+    if (!vt || !pc) return fail(c, DIT_EHIP, "hipGetSymbolAddress returned no address");
+    d.pieces = (char*)pc;
+    d.vt = vt;
+  }
+  *out = &d;
+  return DIT_OK;
+}
+
+// A slot of the piece array for the time of one call (the calls return after
+// their stream has drained).  With every slot taken by calls of other threads
+// the launch runs without one: whole query blocks or tiles only, the same
+// result up to the rounding of the sums.
+struct PieceSlot {
+  DeviceScratch* d;
+  int slot = -1;
+  PieceSlot(DeviceScratch* d_, size_t bytes) : d(d_) {
+    if (bytes == 0 || bytes > kPieceBytes) return;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    for (int i = 0; i < kPieceSlots && slot < 0; ++i)
+      if (!d->used[i]) {
+        d->used[i] = true;
+        slot = i;
+      }
+  }
+  ~PieceSlot() {
+    if (slot < 0) return;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    d->used[slot] = false;
+  }
+  PieceSlot(const PieceSlot&) = delete;
+  PieceSlot& operator=(const PieceSlot&) = delete;
+  float* get() const { return slot < 0 ? nullptr : (float*)(d->pieces + slot * kPieceBytes); }
+};
+
+dit_status gemm_call(const GemmArgs& g, hipStream_t s) {
+  dit_cache* c = nullptr;
+  int dev = 0, ncu = 256;
+  hipGetDevice(&dev);
+  hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  DeviceScratch* d = nullptr;
+  TRY(device_scratch(&d));
+  const PieceSlot ws(d, dit::gemm_bf16_uses_ws(&g, 1, ncu) ? dit::gemm_bf16_ws_bytes(ncu) : 0);
+  const hipError_t e = dit::launch_gemm_bf16(&g, 1, s, ncu, ws.get());
+  const hipError_t done = hipStreamSynchronize(s);  // the slot is free only after it
+  HIPCK(e);
+  HIPCK(done);
+  return DIT_OK;
+}
+
+dit_status attention_call(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v, int64_t ldv, void* o,
+                          int64_t ldo, int Lq, int Lk, int heads, int flags, void* vt, DeviceScratch* d,
+                          hipStream_t s) {
+  dit_cache* c = nullptr;
+  int dev = 0, ncu = 256;
+  hipGetDevice(&dev);
+  hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  const bool bounded = (flags & DIT_ATTN_BOUNDED_LOGITS) != 0;
+  const PieceSlot ws(d, dit::flash_attn_ws_bytes(Lq, Lk, heads, 1, ncu));
+  hipError_t e = dit::launch_transpose_v_bf16(v, ldv, vt, Lk, heads, s);
+  if (e == hipSuccess)
+    e = dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads, bounded, s, ncu,
+                                    ws.get());
+  const hipError_t done = hipStreamSynchronize(s);  // the slot is free only after it
+  HIPCK(e);
+  HIPCK(done);
+  return DIT_OK;
+}
+
+dit_status check_attention(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v, int64_t ldv,
+                           const void* o, int64_t ldo, int32_t Lq, int32_t Lk, int32_t heads, int32_t flags) {
+  dit_cache* c = nullptr;
+  if (!q || !k || !v || !o) return fail(c, DIT_EINVAL, "null argument");
+  if (Lq < 1 || Lk < 1 || heads < 1) return fail(c, DIT_ESHAPE, "bad attention shape");
+  if (flags & ~DIT_ATTN_BOUNDED_LOGITS) return fail(c, DIT_EINVAL, "bad attention flags");
+  if (ldq < heads * 128 || ldk < heads * 128 || ldv < heads * 128 || ldo < heads * 128)
+    return fail(c, DIT_ESHAPE, "row stride smaller than heads*128");
+  return DIT_OK;
+}
+}  // namespace
+
 // ====================================================================== C ABI
 extern "C" {
 
@@ -1640,7 +1766,7 @@ void dit_cache_destroy(dit_cache* c) {
   if (c->stream) hipStreamSynchronize(c->stream);
   free_per_call(c);
   for (Lane& l : c->lanes) free_lane(l);
-  void* ps[] = {c->wdev, c->xs, c->X, c->A, c->Y, c->vt, c->modq, c->attn_ws, c->yf, c->vel, c->ones,
+  void* ps[] = {c->wdev, c->xs, c->X, c->A, c->Y, c->vt, c->modq, c->pieces, c->yf, c->vel, c->ones,
                 c->partials, c->cand, c->st_hi, c->st_lo};
   for (void* p : ps)
     if (p) hipFree(p);
@@ -1690,115 +1816,12 @@ dit_status dit_gemm_bf16(const dit_gemm_desc* d, void* hip_stream) {
   g.C = d->C; g.ldc = d->ldc; g.gate = d->gate; g.M = d->M; g.N = d->N; g.K = d->K;
   g.flags = d->flags; g.rms_cols = d->rms_cols;
   g.gelu_from = d->gelu_from; g.gap_at = d->gap ? d->gap_at : 0x7fffffff; g.gap = d->gap;
-  int dev = 0, ncu = 256;
-  hipGetDevice(&dev);
-  hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  hipStream_t s = (hipStream_t)hip_stream;
-  HIPCK(dit::launch_gemm_bf16(&g, 1, s, ncu));
-  HIPCK(hipStreamSynchronize(s));
-  return DIT_OK;
+  return gemm_call(g, (hipStream_t)hip_stream);
 }
 
 }  // extern "C"
 
 // ------------------------------------------------------- attention alone
-// Device memory of the attention entry points, which allocate nothing:
-// transposed values of dit_attention_bf16_noalloc, and the pieces of shared
-// attention items of both.  In host code these names are host-side
-// stand-ins, not device memory: kernels take the addresses that
-// hipGetSymbolAddress returns for the current device.
-static __device__ __align__(256) uint16_t scratch[DIT_NOALLOC_VT_MAX_ELEMS];
-namespace {
-constexpr int kPieceSlots = 2;                     // calls in flight on one GPU that may share items
-constexpr size_t kPieceBytes = (size_t)66 << 20;   // flash_attn_ws_bytes of 256 CUs (65 MiB)
-}  // namespace
-static __device__ __align__(256) unsigned char pieces[kPieceSlots * kPieceBytes];
-
-namespace {
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-struct DeviceScratch {
-  void* vt = nullptr;
-  char* pieces = nullptr;
-  bool used[kPieceSlots] = {};
-} g_scratch[kMaxDevices];
-
-// The current device's copies of the arrays, looked up once per device.
-dit_status device_scratch(DeviceScratch** out) {
-  dit_cache* c = nullptr;
-  int dev = -1;
-  HIPCK(hipGetDevice(&dev));
-  if (dev < 0 || dev >= kMaxDevices) return fail(c, DIT_EINVAL, "device index out of range");
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  DeviceScratch& d = g_scratch[dev];
-  if (!d.vt) {
-    void *vt = nullptr, *pc = nullptr;
-    HIPCK(hipGetSymbolAddress(&vt, HIP_SYMBOL(scratch)));
-    HIPCK(hipGetSymbolAddress(&pc, HIP_SYMBOL(pieces)));
-    if (!vt || !pc) return fail(c, DIT_EHIP, "hipGetSymbolAddress returned no address");
-    d.pieces = (char*)pc;
-    d.vt = vt;
-  }
-  *out = &d;
-  return DIT_OK;
-}
-
-// A slot of the piece array for the time of one call (the calls return after
-// their stream has drained).  With every slot taken by calls of other threads
-// the launch runs without one: whole query blocks only, the same result up
-// to the rounding of the sums.
-struct PieceSlot {
-  DeviceScratch* d;
-  int slot = -1;
-  PieceSlot(DeviceScratch* d_, size_t bytes) : d(d_) {
-    if (bytes == 0 || bytes > kPieceBytes) return;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    for (int i = 0; i < kPieceSlots && slot < 0; ++i)
-      if (!d->used[i]) {
-        d->used[i] = true;
-        slot = i;
-      }
-  }
-  ~PieceSlot() {
-    if (slot < 0) return;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    d->used[slot] = false;
-  }
-  PieceSlot(const PieceSlot&) = delete;
-  PieceSlot& operator=(const PieceSlot&) = delete;
-  float* get() const { return slot < 0 ? nullptr : (float*)(d->pieces + slot * kPieceBytes); }
-};
-
-dit_status attention_call(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v, int64_t ldv, void* o,
-                          int64_t ldo, int Lq, int Lk, int heads, int flags, void* vt, DeviceScratch* d,
-                          hipStream_t s) {
-  dit_cache* c = nullptr;
-  int dev = 0, ncu = 256;
-  hipGetDevice(&dev);
-  hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  const PieceSlot ws(d, dit::flash_attn_ws_bytes(Lq, Lk, heads, 1, ncu));
-  hipError_t e = dit::launch_transpose_v_bf16(v, ldv, vt, Lk, heads, s);
-  if (e == hipSuccess)
-    e = dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads,
-                                    (flags & DIT_ATTN_BOUNDED_LOGITS) != 0, s, ncu, ws.get());
-  const hipError_t done = hipStreamSynchronize(s);  // the slot is free only after it
-  HIPCK(e);
-  HIPCK(done);
-  return DIT_OK;
-}
-
-dit_status check_attention(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v, int64_t ldv,
-                           const void* o, int64_t ldo, int32_t Lq, int32_t Lk, int32_t heads, int32_t flags) {
-  dit_cache* c = nullptr;
-  if (!q || !k || !v || !o) return fail(c, DIT_EINVAL, "null argument");
-  if (Lq < 1 || Lk < 1 || heads < 1) return fail(c, DIT_ESHAPE, "bad attention shape");
-  if (flags & ~DIT_ATTN_BOUNDED_LOGITS) return fail(c, DIT_EINVAL, "bad attention flags");
-  if (ldq < heads * 128 || ldk < heads * 128 || ldv < heads * 128 || ldo < heads * 128)
-    return fail(c, DIT_ESHAPE, "row stride smaller than heads*128");
-  return DIT_OK;
-}
-}  // namespace
-
 extern "C" dit_status dit_attention_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v,
                                          int64_t ldv, void* o, int64_t ldo, int32_t Lq, int32_t Lk, int32_t heads,
                                          int32_t flags, void* vt_ws, void* hip_stream) {

@@ -13,6 +13,7 @@
 // two-stage pipeline on 32x32x16 MFMAs.
 // Workgroups are remapped so that each of the 8 XCDs walks a contiguous,
 // M-grouped range of tiles (its own L2 sees the shared A rows / W columns).
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -42,6 +43,10 @@ struct Prob {
 struct Batch {
   Prob p0, p1;
   int tiles0, total;
+  // Ring kernel: tiles past `whole` are computed in `parts` shares of K each,
+  // as f32 pieces in ws for gemm_finish_kernel; total counts the pieces.
+  int whole, parts;
+  float* ws;
 };
 
 __device__ __forceinline__ int xcd_remap(int bid, int n) {
@@ -711,6 +716,23 @@ __device__ __forceinline__ void store_vt(const Prob& P, const f32x4_t (&acc)[4][
     }
   }
 }
+// Problem and origin of 256 x 256 tile lt of a launch: M-grouped order, eight
+// tile rows per group.
+__device__ __forceinline__ void ring_tile(const Batch& b, int lt, Prob& P, int& m0, int& n0) {
+  const bool second = lt >= b.tiles0;
+  P = second ? b.p1 : b.p0;
+  if (second) lt -= b.tiles0;
+  constexpr int GROUP = 8;
+  const int in_group = GROUP * P.tiles_n;
+  const int gid = lt / in_group;
+  const int first_m = gid * GROUP;
+  const int gsz = min(P.tiles_m - first_m, GROUP);
+  m0 = (first_m + (lt % in_group) % gsz) * 256;
+  n0 = (lt % in_group) / gsz * 256;
+}
+
+constexpr int PIECE_WAVE = 64 * 128;  // floats of a wave's part of a piece, in register order
+
 // 256 x 256 tiles, 8 waves of 64 x 128, BK = 64, with the whole 160 KB of
 // LDS as a ring of five 32 KB operand slices: operand i (W slice s = 2s,
 // A slice s = 2s + 1) lives in unit i % 5.  W slices are copied two slices
@@ -742,18 +764,17 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(Batch b) {
   __shared__ __attribute__((aligned(1024))) char smem[5 * UNIT];
 
   if ((int)blockIdx.x >= b.total) return;
-  int lt = xcd_remap(blockIdx.x, b.total);
-  const bool second = lt >= b.tiles0;
-  Prob P = second ? b.p1 : b.p0;
-  if (second) lt -= b.tiles0;
-  constexpr int GROUP = 8;
-  const int in_group = GROUP * P.tiles_n;
-  const int gid = lt / in_group;
-  const int first_m = gid * GROUP;
-  const int gsz = min(P.tiles_m - first_m, GROUP);
-  const int tm = first_m + (lt % in_group) % gsz;
-  const int tn = (lt % in_group) / gsz;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int piece = (int)blockIdx.x - b.whole;  // < 0: a whole tile
+  Prob P;
+  int m0, n0;
+  ring_tile(b, piece < 0 ? xcd_remap(blockIdx.x, b.whole) : b.whole + piece / b.parts, P, m0, n0);
+  int nk = P.K / BK_;  // >= 2
+  if (piece >= 0) {
+    const int part = piece % b.parts, k0 = nk * part / b.parts, k1 = nk * (part + 1) / b.parts;
+    P.A += (int64_t)k0 * BK_;
+    P.W += (int64_t)k0 * BK_;
+    nk = k1 - k0;
+  }
   // per-segment gate vectors: the host admits only BM | gseg
   if (P.gseg > 0) P.gate += (int64_t)(m0 / P.gseg) * P.gstride;
 
@@ -824,7 +845,6 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(Batch b) {
   using yes = std::integral_constant<bool, true>;
   using no = std::integral_constant<bool, false>;
 
-  const int nk = P.K / BK_;  // >= 2
   bf16x8_t a0[TM], b0[TN], a1[TM], b1[TN];
   // unit offsets of W kt, A kt, W kt+1, A kt+1, W kt+2
   int u0 = 0, u1 = UNIT, u2 = 2 * UNIT, u3 = 3 * UNIT, u4 = 4 * UNIT;
@@ -859,6 +879,14 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(Batch b) {
   slice(nk - 2, no{});
   rd(u0, u1, 1, a1, b1); mm(a0, b0); sched(no{});
   mm(a1, b1);
+  if (piece >= 0) {
+    float* w = b.ws + ((int64_t)piece * 8 + wave) * PIECE_WAVE + 4 * lane;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) *(f32x4_t*)(w + (i * TN + j) * 256) = acc[i][j];
+    return;
+  }
   __syncthreads();  // every wave is done with the ring before the epilogue reuses LDS
   if constexpr (KIND == EPI_K_STORE) {
     const int ncol0 = n0 + wn * WN;  // wave-uniform: whole head groups are values or not
@@ -868,6 +896,44 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(Batch b) {
     }
   }
   if constexpr (KIND != EPI_K_STORE) epi.prep();
+  uint2 old[2][8][2];
+  if (epi.gated) { epi.load_old(0, old[0]); epi.load_old(1, old[1]); }
+  epi.slab_pass16(acc[0], acc[1], 0, old[0], lr, lq);
+  epi.slab_pass16(acc[2], acc[3], 1, old[1], lr, lq);
+}
+
+// Adds the pieces of one wave's part (64 x 128) of a tile in the order of K and
+// runs the ring kernel's epilogue on the sum.  One wave per work-group: 64
+// rows x one head group need nothing from the tile's other parts.
+template <int KIND>
+__global__ __launch_bounds__(64) void gemm_finish_kernel(Batch b) {
+  __shared__ float slab[32 * 128];
+  const int t = blockIdx.x >> 3, wave = blockIdx.x & 7;
+  Prob P;
+  int m0, n0;
+  ring_tile(b, b.whole + t, P, m0, n0);
+  if (P.gseg > 0) P.gate += (int64_t)(m0 / P.gseg) * P.gstride;
+  const int lane = threadIdx.x, wm = wave >> 1, wn = wave & 1, lr = lane & 15, lq = lane >> 4;
+  f32x4_t acc[4][8];
+  for (int p = 0; p < b.parts; ++p) {
+    const float* w = b.ws + (((int64_t)t * b.parts + p) * 8 + wave) * PIECE_WAVE + 4 * lane;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const f32x4_t v = *(const f32x4_t*)(w + (i * 8 + j) * 256);
+        acc[i][j] = p ? acc[i][j] + v : v;
+      }
+  }
+  const int ncol0 = n0 + 128 * wn;
+  if constexpr (KIND == EPI_K_STORE) {
+    if (P.vt && ncol0 >= P.vt_col0 && ncol0 < P.vt_col0 + 128 * P.vt_heads) {
+      store_vt(P, acc, m0 + 64 * wm, ncol0, lr, lq);
+      return;
+    }
+  }
+  EpiLds<KIND> epi(P, m0 + 64 * wm, ncol0, lane & 31, lane >> 5, slab);
+  epi.prep();
   uint2 old[2][8][2];
   if (epi.gated) { epi.load_old(0, old[0]); epi.load_old(1, old[1]); }
   epi.slab_pass16(acc[0], acc[1], 0, old[0], lr, lq);
@@ -1060,6 +1126,8 @@ __global__ __launch_bounds__(256) void proj_small_n_kernel(const bf16_t* __restr
   }
 }
 
+constexpr int SPLIT_MIN_SLICES = 24;
+
 struct Cfg {
   int bm, bn, wn, wg_per_cu, threads, bk;
   bool lds_epi;
@@ -1080,7 +1148,7 @@ struct Cfg {
    kLdsEpilogue<BN / WGN, WGM * WGN, ST * (BM + BN) * BK_ * 2>, EFF, true,                     \
    gemm_bf16_dma_kernel<BM, BN, WGM, WGN, BK_, ST>, 0}
 const Cfg kCfgs[] = {
-    {256, 256, 128, 1, 512, 64, true, 1.02f, true, gemm_bf16_ring_kernel<EPI_K_ANY>, 128},
+    {256, 256, 128, 1, 512, 64, true, 1.08f, true, gemm_bf16_ring_kernel<EPI_K_ANY>, 128},
     DIT_DMA_CFG(256, 256, 4, 2, 64, 2, 1, 1.00f),
     DIT_DMA_CFG(256, 128, 4, 1, 64, 2, 1, 0.72f),
     DIT_DMA_CFG(128, 128, 4, 1, 64, 2, 2, 0.85f),
@@ -1115,7 +1183,25 @@ Prob make_prob(const GemmArgs& g, int bm, int bn) {
   return p;
 }
 
-int pick_cfg(const GemmArgs* g, int n, int n_cu) {
+// Shares of K for the tiles of a ring launch past the last whole round (0:
+// they stay whole).  Where they fill at most half the chip, the shares take
+// nk / parts slices (1.2 us each) instead of nk; writing, adding and the
+// second launch cost about 20 us.  Through the entry point, whole tiles (or the
+// 128 x 128 ones chosen instead) against shares: 6144 x 3072 x 15360 gated (288
+// tiles) 724 -> 429 us, 6144 x 3072 x 3072 154 -> 123, 16896 x 3072 x 12288 (792)
+// 1145 -> 941, 6144 x 4096 x 8192 (384, two shares) 407 -> 323; 16896 x 9216 x
+// 3072 (2376 tiles, 3 shares of 16 slices) no change.  Past half the chip the
+// pieces (256 KB each, written and read) outweigh the idle CUs.
+int ring_parts(long tiles, const GemmArgs* g, int n, int n_cu) {
+  const long rem = tiles % n_cu;
+  if (tiles < n_cu || rem == 0) return 0;
+  int nk = g[0].K / 64;
+  for (int i = 1; i < n; ++i) nk = std::min(nk, g[i].K / 64);
+  const int parts = (int)std::min<long>(n_cu / rem, nk / 4);
+  return parts >= 2 && nk - nk / parts >= SPLIT_MIN_SLICES ? parts : 0;
+}
+
+int pick_cfg(const GemmArgs* g, int n, int n_cu, bool ws) {
   bool rms = false, aligned = true;
   for (int i = 0; i < n; ++i) {
     rms |= g[i].rms_cols > 0;
@@ -1170,8 +1256,11 @@ int pick_cfg(const GemmArgs* g, int n, int n_cu) {
     if (!admits(k)) continue;
     const long tiles = tiles_of(k.bm, k.bn);
     const long slots = (long)n_cu * k.wg_per_cu;
-    const long rounds = (tiles + slots - 1) / slots;
-    const double t = (double)rounds * k.bm * k.bn * k.wg_per_cu / k.eff;
+    double rounds = (double)((tiles + slots - 1) / slots);
+    if (c == 0 && ws)
+      if (const int parts = ring_parts(tiles, g, n, n_cu))
+        rounds = tiles / n_cu + 1.0 / parts + 17.0 * 64 / g[0].K;  // 20 us in slices
+    const double t = rounds * k.bm * k.bn * k.wg_per_cu / k.eff;
     if (t < best_t) { best_t = t; best = c; }
   }
   return best;
@@ -1242,17 +1331,26 @@ static bool vt_ok(const GemmArgs* g, int n, int c) {
   return true;
 }
 
-bool gemm_bf16_fuses_vt(const GemmArgs* g, int n, int n_cu) {
+bool gemm_bf16_fuses_vt(const GemmArgs* g, int n, int n_cu, bool ws) {
   if (n < 1 || n > 2) return false;
-  return vt_ok(g, n, pick_cfg(g, n, n_cu));
+  return vt_ok(g, n, pick_cfg(g, n, n_cu, ws));
 }
 
-hipError_t launch_gemm_bf16(const GemmArgs* g, int n, hipStream_t stream, int n_cu) {
+bool gemm_bf16_uses_ws(const GemmArgs* g, int n, int n_cu) {
+  if (pick_cfg(g, n, n_cu, true) != 0) return false;
+  long tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += (long)((g[i].M + 255) / 256) * ((g[i].N + 255) / 256);
+  return ring_parts(tiles, g, n, n_cu) > 0;
+}
+
+size_t gemm_bf16_ws_bytes(int n_cu) { return (size_t)n_cu * 8 * PIECE_WAVE * sizeof(float); }
+
+hipError_t launch_gemm_bf16(const GemmArgs* g, int n, hipStream_t stream, int n_cu, float* ws) {
   if (n < 1 || n > 2) return hipErrorInvalidValue;
   for (int i = 0; i < n; ++i)
     if (g[i].gseg < 0 || (g[i].gseg > 0 && (g[i].gseg % 32 || !(g[i].flags & DIT_EPI_GATED_RES))))
       return hipErrorInvalidValue;
-  const int c = pick_cfg(g, n, n_cu);
+  const int c = pick_cfg(g, n, n_cu, ws != nullptr);
   if (c < 0) return hipErrorInvalidValue;
   bool want_vt = false;
   for (int i = 0; i < n; ++i) want_vt |= g[i].vt != nullptr;
@@ -1265,7 +1363,24 @@ hipError_t launch_gemm_bf16(const GemmArgs* g, int n, hipStream_t stream, int n_
   b.tiles0 = b.p0.tiles_m * b.p0.tiles_n;
   b.total = b.tiles0 + (n > 1 ? b.p1.tiles_m * b.p1.tiles_n : 0);
   if (b.total == 0) return hipSuccess;
+  b.whole = b.total;
+  b.parts = 1;
+  b.ws = ws;
+  int rem = 0;
+  if (c == 0 && ws)
+    if (const int parts = ring_parts(b.total, g, n, n_cu)) {
+      rem = b.total % n_cu;
+      b.parts = parts;
+      b.whole = b.total - rem;
+      b.total = b.whole + rem * parts;
+    }
   hipLaunchKernelGGL(fn, dim3(b.total), dim3(k.threads), 0, stream, b);
+  if (rem) {
+    void (*fin)(Batch) = fn == gemm_bf16_ring_kernel<EPI_K_STORE>   ? gemm_finish_kernel<EPI_K_STORE>
+                         : fn == gemm_bf16_ring_kernel<EPI_K_GATED> ? gemm_finish_kernel<EPI_K_GATED>
+                                                                    : gemm_finish_kernel<EPI_K_ANY>;
+    hipLaunchKernelGGL(fin, dim3(8 * rem), dim3(64), 0, stream, b);
+  }
   return hipGetLastError();
 }
 

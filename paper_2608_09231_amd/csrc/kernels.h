@@ -47,12 +47,16 @@ struct GemmArgs {
 
 // bf16 MFMA GEMM; n = 1 or 2 independent problems in one launch.  Invalid
 // arguments (no tile configuration admits the problem) return an error.
-hipError_t launch_gemm_bf16(const GemmArgs* g, int n, hipStream_t s, int n_cu);
+// ws: workspace of gemm_bf16_ws_bytes, with which a last round of few tiles is
+// shared out over K, or nullptr.
+hipError_t launch_gemm_bf16(const GemmArgs* g, int n, hipStream_t s, int n_cu, float* ws);
+size_t gemm_bf16_ws_bytes(int n_cu);
+bool gemm_bf16_uses_ws(const GemmArgs* g, int n, int n_cu);  // whether the launch would
 // Whether launch_gemm_bf16 can write the transposed values of these problems
 // itself (the vt fields set): 128-column head groups, 32-row aligned segments
 // and the 256 x 256 kernel.  Otherwise the caller leaves vt unset and
 // transposes the values with launch_transpose_v_bf16.
-bool gemm_bf16_fuses_vt(const GemmArgs* g, int n, int n_cu);
+bool gemm_bf16_fuses_vt(const GemmArgs* g, int n, int n_cu, bool ws);
 // v = A W^T + bias for N <= 128 (multiple of 16), K % 32 == 0, f32 output; with
 // x != nullptr the result goes into the Euler update x += alpha * v instead.
 hipError_t launch_proj_small_n(const void* A, int64_t lda, const void* W, int64_t ldw, const void* bias,

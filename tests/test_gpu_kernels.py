@@ -176,6 +176,43 @@ def test_gemm_few_rows(M, N, K, flags):
     assert_bf16_close(host_bf16(out), round_bf16(y))
 
 
+@pytest.mark.parametrize("M,N,K,flags", [
+    (4300, 4104, 2112, binding.EPI_STORE),       # 289 tiles: 33 shared out in 7 uneven parts of 33 slices
+    (4300, 4104, 2112, binding.EPI_GATED_RES),
+    (4100, 4360, 1600, binding.EPI_F32),         # 306 tiles: 50 in 5
+    (4096, 6144, 4096, binding.EPI_STORE),       # 384 tiles: 128 in 2
+])
+def test_gemm_ring_last_round(M, N, K, flags):
+    """Tiles past the last whole round in shares of K, added by the finishing
+    kernel with the ring kernel's epilogues (norm, GELU and column gap too):
+    sampled rows against float64."""
+    torch = torch_cuda()
+    a_b, a = make((M, K))
+    w_b, w = make((N, K), 0.05)
+    b_b, b = make((N,), 0.1)
+    rows = np.unique(np.concatenate([np.arange(M - 300, M, 7), RNG.choice(M, 60)]))
+    y = a[rows] @ w.T + b
+    gap = 512 if flags == binding.EPI_STORE else 0
+    out = torch.zeros((M, N + gap), dtype=torch.float32 if flags == binding.EPI_F32 else torch.int16, device="cuda")
+    args = dict(M=M, N=N, K=K, ldc=N + gap, flags=flags)
+    if flags == binding.EPI_STORE:
+        args.update(rms_cols=2048, gelu_from=3072, gap_at=3072, gap=gap)
+        ref = np.concatenate([dit.rms_heads(y[:, :2048], 16, 128), y[:, 2048:3072],
+                              np.zeros((len(rows), gap)), dit.gelu_tanh(y[:, 3072:])], axis=1)
+    else:
+        ref = y
+    gate = None
+    if flags == binding.EPI_GATED_RES:
+        c0_b, c0 = make((M, N))
+        g = RNG.standard_normal(N).astype(np.float32)
+        out, gate, ref = dev(torch, c0_b), dev(torch, g), c0[rows] + g.astype(np.float64) * y
+    binding.gemm_bf16(dev(torch, a_b), dev(torch, w_b), dev(torch, b_b), out, gate=gate, **args)
+    if flags == binding.EPI_F32:
+        np.testing.assert_allclose(out.cpu().numpy()[rows], ref, rtol=1e-5, atol=3e-5)
+    else:
+        assert_bf16_close(host_bf16(out)[rows], round_bf16(ref))
+
+
 def test_gemm_ring_rms_gelu_gap_ragged():
     """The ring kernel's store epilogue with the single-block projection's
     column roles at a ragged M: per-head RMS on the first 2 H columns, GELU
