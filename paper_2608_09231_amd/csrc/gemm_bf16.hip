@@ -1080,46 +1080,67 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_small_kernel(Batch b) {
 
 // Small-N projection (the final layer, N = C <= 128): v[m][c] = sum_k A[m][k] W[c][k]
 // + bias[c], or with x != nullptr the Euler update x[m][c] += alpha * v[m][c]
-// fused in.  16 rows per workgroup, the K range split over 4 waves, MFMA
+// fused in.  16 RB rows per workgroup, the K range split over 8 waves, MFMA
 // 16x16x32 bf16; A rows stream from HBM once, W (N x K, a few hundred KB)
-// stays in L2.  The 4 partial tiles are summed through LDS in wave order.
-template <int NT>  // N / 16 output tiles
-__global__ __launch_bounds__(256) void proj_small_n_kernel(const bf16_t* __restrict__ A, int64_t lda,
+// stays in L2.  The 8 partial tiles are summed through LDS in wave order.
+// What bounds it is loads in flight and, at many rows, the L2 reads of W, so
+// three steps' loads are issued together and RB = 2 halves those reads.
+// Kernel time with four waves, one step in flight and 16 rows -> now: 4096 x 64 x
+// 3072 41 -> 21, 1024 x 64 x 3072 28 -> 20, 32760 x 64 x 5120 290 -> 170 us.
+template <int NT, int RB>  // N / 16 output tiles, 16-row blocks
+__global__ __launch_bounds__(512) void proj_small_n_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                            const bf16_t* __restrict__ W, int64_t ldw,
                                                            const bf16_t* __restrict__ bias, float* out,
                                                            int64_t ldo, float* x, int64_t ldx, float alpha,
                                                            int M, int K) {
-  __shared__ float part[4][16][NT * 16 + 1];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m0 = blockIdx.x * 16;
+  constexpr int KS = 8, U = 3;
+  __shared__ float part[KS][16 * RB][NT * 16 + 1];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = blockIdx.x * 16 * RB;
   const int lr = lane & 15, lq = lane >> 4;  // row / column within 16, k-quarter of the 32-deep step
-  const int row = min(m0 + lr, M - 1);
-  const int ksteps = K / 32, per = (ksteps + 3) / 4;
+  const int ksteps = K / 32, per = (ksteps + KS - 1) / KS;
   const int s0 = wave * per, s1 = min(ksteps, s0 + per);
-  f32x4_t acc[NT];
+  f32x4_t acc[RB][NT] = {};
+  const bf16_t* ap[RB];
 #pragma unroll
-  for (int j = 0; j < NT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  const bf16_t* ap = A + (int64_t)row * lda + 8 * lq;
+  for (int i = 0; i < RB; ++i) ap[i] = A + (int64_t)min(m0 + 16 * i + lr, M - 1) * lda + 8 * lq;
   const bf16_t* wp = W + (int64_t)lr * ldw + 8 * lq;
-  for (int st = s0; st < s1; ++st) {
-    const bf16x8_t a = __builtin_bit_cast(bf16x8_t, *(const uint4*)(ap + 32 * st));
+  for (int st = s0; st < s1; st += U) {
+    bf16x8_t a[U][RB], w[U][NT];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const bf16x8_t w = __builtin_bit_cast(bf16x8_t, *(const uint4*)(wp + (int64_t)16 * j * ldw + 32 * st));
-      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w, acc[j], 0, 0, 0);
+    for (int u = 0; u < U; ++u) {
+      if (st + u >= s1) break;
+#pragma unroll
+      for (int i = 0; i < RB; ++i) a[u][i] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(ap[i] + 32 * (st + u)));
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        w[u][j] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(wp + (int64_t)16 * j * ldw + 32 * (st + u)));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (st + u >= s1) break;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][i], w[u][j], acc[i][j], 0, 0, 0);
     }
   }
-  // acc[j][i] = C[row 4 lq + i][col 16 j + lr]
+  // acc[i][j][r] = C[row 16 i + 4 lq + r][col 16 j + lr]
 #pragma unroll
-  for (int j = 0; j < NT; ++j)
+  for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) part[wave][4 * lq + i][16 * j + lr] = acc[j][i];
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[wave][16 * i + 4 * lq + r][16 * j + lr] = acc[i][j][r];
   __syncthreads();
-  for (int e = threadIdx.x; e < 16 * NT * 16; e += 256) {
+  for (int e = threadIdx.x; e < 16 * RB * NT * 16; e += 512) {
     const int r = e / (NT * 16), c = e % (NT * 16);
     const int m = m0 + r;
     if (m >= M) continue;
-    float v = part[0][r][c] + part[1][r][c] + part[2][r][c] + part[3][r][c];
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < KS; ++w) v += part[w][r][c];
     if (bias) v += bf16_to_f32(bias[c]);
     if (x) x[(int64_t)m * ldx + c] += alpha * v;
     else out[(int64_t)m * ldo + c] = v;
@@ -1272,11 +1293,14 @@ hipError_t launch_proj_small_n(const void* A, int64_t lda, const void* W, int64_
                                float* out, int64_t ldo, float* x, int64_t ldx, float alpha, int M, int N,
                                int K, hipStream_t s) {
   if (K % 32 || N % 16 || N > 128 || M < 1) return hipErrorInvalidValue;
-  const dim3 grid((M + 15) / 16);
-#define DIT_PROJ(NT_)                                                                             \
-  case NT_:                                                                                       \
-    hipLaunchKernelGGL(proj_small_n_kernel<NT_>, grid, dim3(256), 0, s, (const bf16_t*)A, lda,     \
-                       (const bf16_t*)W, ldw, (const bf16_t*)bias, out, ldo, x, ldx, alpha, M, K); \
+  // 32 rows a work-group where those still give every CU two of them
+  const bool two = M >= 32 * 512;
+  const dim3 grid((M + (two ? 31 : 15)) / (two ? 32 : 16));
+#define DIT_PROJ(NT_)                                                                                  \
+  case NT_:                                                                                            \
+    hipLaunchKernelGGL((two ? proj_small_n_kernel<NT_, 2> : proj_small_n_kernel<NT_, 1>), grid,        \
+                       dim3(512), 0, s, (const bf16_t*)A, lda, (const bf16_t*)W, ldw,                  \
+                       (const bf16_t*)bias, out, ldo, x, ldx, alpha, M, K);                            \
     break;
   switch (N / 16) {
     DIT_PROJ(1) DIT_PROJ(2) DIT_PROJ(3) DIT_PROJ(4) DIT_PROJ(5) DIT_PROJ(6) DIT_PROJ(7) DIT_PROJ(8)
