@@ -72,7 +72,7 @@ enum {
  * ldq), k and v [Lk, heads*128] (ldk, ldv), o [Lq, heads*128] (ldo);
  * head h occupies columns [128h, 128h + 128).  flags: 0 or
  * DIT_ATTN_BOUNDED_LOGITS.  vt_ws is a device workspace of heads * 128 *
- * round_up(Lk, 64) bf16 elements that receives v transposed per head.  Where
+ * round_up(Lk, 64) bf16 elements for v transposed per head.  Where
  * the work fills the chip's CUs only partly in its last round, the key ranges
  * are shared out and the parts added from f32 sums in device memory of the
  * library; with more than two such calls in flight on one GPU the further ones

@@ -90,6 +90,7 @@ constexpr int PSTAGE = 5;
 // this many tiles (about 1.7 us each): the second launch and the pieces' round
 // trip take 12-17 us at the shapes above.
 constexpr int SPLIT_MIN_TILES = 8;
+constexpr int SMALL_MAX_KEYS = 1280;
 constexpr int NW = 8;          // waves per work-group, 32 queries each
 constexpr int QB = 32 * NW;    // queries per item
 constexpr int CPW = 16 / NW;   // 1 KB copies per wave for each of K and V^T
@@ -651,6 +652,151 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(bf16_t* __restrict__ 
                                         pack_bf16x2(acc[d][2] * inv, acc[d][3] * inv));
 }
 
+// Few, short sequences: 32 queries of a head per work-group, the 32-key blocks
+// dealt out to its eight waves, operands straight from global memory (V too:
+// no transposed copy, no launch for one).  What bounds such a launch is its
+// chain of latencies: the kernel above fills and drains a five-stage pipeline
+// on a work-group per 256 queries.  The same products, roundings and f32
+// statistics; the eight waves' outputs meet in LDS.  Through the entry point
+// (about 11 us of it launch and wait), one work-group per 256 queries -> now:
+// 1 x 1 18.9 -> 14.8 us, 240 x 240, 2 heads 31.2 -> 19.5, 1000 x 1000, 8 heads 48.0
+// -> 29.3, 256 x 1000, 32 heads without a bound 55.4 -> 37.4.
+template <bool BOUNDED>
+__global__ __launch_bounds__(512) void flash_attn_small_kernel(
+    const bf16_t* __restrict__ q, int64_t ldq, const bf16_t* __restrict__ k, int64_t ldk,
+    const bf16_t* __restrict__ v, int64_t ldv, bf16_t* __restrict__ o, int64_t ldo, int Lq, int Lk,
+    float scale_log2, SeqMap sm) {
+  constexpr int LD = D + 4;
+  __shared__ __attribute__((aligned(16))) float so[8][32][LD];
+  __shared__ float sl[8][32], smax[8][32];
+  const RowMap rm = sm.at(blockIdx.z);
+  const int h = blockIdx.y, q0 = blockIdx.x * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lq = lane >> 4;
+  bf16x8_t qf[2][4];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const bf16_t* p = q + rm(min(q0 + 16 * g + lr, Lq - 1)) * ldq + h * D + 8 * lq;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) qf[g][s] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(p + 32 * s));
+  }
+  f32x4_t acc[8][2] = {};
+  float m[2], l[2] = {0.f, 0.f};
+  m[0] = m[1] = BOUNDED ? BOUNDED_SHIFT_LOG2 : -INFINITY;
+  const bf16x2_t ones = {(__bf16)1.f, (__bf16)1.f};
+  const int blocks = (Lk + 31) / 32;
+  for (int b = wave; b < blocks; b += 8) {
+    const int k0 = 32 * b;
+    bf16x8_t kf[2][4];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const bf16_t* p = k + rm(min(k0 + 16 * kb + lr, Lk - 1)) * ldk + h * D + 8 * lq;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) kf[kb][s] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(p + 32 * s));
+    }
+    // V^T fragment dt: d = 16 dt + lr, slot 8 lq + e of the block is key 16 (e >> 2) + 4 lq + (e & 3)
+    uint32_t vw[8][4];
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      const int key = k0 + 16 * (e >> 2) + 4 * lq + (e & 3);
+      const bf16_t* p0 = v + rm(min(key, Lk - 1)) * ldv + h * D + lr;
+      const bf16_t* p1 = v + rm(min(key + 1, Lk - 1)) * ldv + h * D + lr;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) vw[dt][e >> 1] = p0[16 * dt] | ((uint32_t)p1[16 * dt] << 16);
+    }
+    f32x4_t s[2][2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        s[kb][g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          s[kb][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][t], qf[g][t], s[kb][g], 0, 0, 0);
+      }
+    // keys past the last one: no probability, and zeros for V (0 times what lies there may be a NaN)
+    const bool ragged = k0 + 32 > Lk;
+    if (ragged) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (k0 + 16 * kb + 4 * lq + r >= Lk) s[kb][0][r] = s[kb][1][r] = -INFINITY;
+    }
+    bf16x8_t pf[2];
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      if constexpr (!BOUNDED) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[kb][g][r]);
+        mx = max_quarters(mx) * scale_log2;
+        const float mn = mx > m[g] + RESCALE_SLACK ? mx : m[g];
+        const float a = __builtin_amdgcn_exp2f(m[g] - mn);
+        if (mn != m[g]) {
+          l[g] *= a;
+#pragma unroll
+          for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[dt][g][r] *= a;
+        }
+        m[g] = mn;
+      }
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 1][g][2 * (e & 1)], scale_log2, -m[g]));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 1][g][2 * (e & 1) + 1], scale_log2, -m[g]));
+        w[e] = pack_bf16x2(p0, p1);
+        l[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w[e]), ones, l[g], false);
+      }
+      pf[g] = __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
+    }
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      if (ragged) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int key = k0 + 16 * (e >> 1) + 4 * lq + 2 * (e & 1);
+          if (key >= Lk) vw[dt][e] = 0;
+          else if (key + 1 >= Lk) vw[dt][e] &= 0xffffu;
+        }
+      }
+      const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, make_uint4(vw[dt][0], vw[dt][1], vw[dt][2], vw[dt][3]));
+#pragma unroll
+      for (int g = 0; g < 2; ++g) acc[dt][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[g], acc[dt][g], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const float ls = sum_quarters(l[g]);
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) *(f32x4_t*)&so[wave][16 * g + lr][16 * dt + 4 * lq] = acc[dt][g];
+    if (lq == 0) {
+      sl[wave][16 * g + lr] = ls;
+      smax[wave][16 * g + lr] = m[g];
+    }
+  }
+  __syncthreads();
+  const int row = tid >> 4, c = 8 * (tid & 15), nw = min(8, blocks);
+  if (q0 + row >= Lq) return;
+  float mx = smax[0][row];
+  for (int w = 1; w < nw; ++w) mx = fmaxf(mx, smax[w][row]);
+  float den = 0.f, y[8] = {};
+  for (int w = 0; w < nw; ++w) {
+    const float a = BOUNDED ? 1.f : __builtin_amdgcn_exp2f(smax[w][row] - mx);
+    den += a * sl[w][row];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] += a * so[w][row][c + e];
+  }
+  const float inv = 1.f / den;
+  uint2* op = (uint2*)(o + rm(q0 + row) * ldo + h * D + c);
+  op[0] = make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
+  op[1] = make_uint2(pack_bf16x2(y[4] * inv, y[5] * inv), pack_bf16x2(y[6] * inv, y[7] * inv));
+}
+
 // vt[h][d][32 g + vt_slot(k)] = v[32 g + k][h*128 + d] for keys < Lk, 0 up to ldvt.
 // 16-byte reads of a 64 x 128 tile into LDS rows of 65 words, then eight
 // halves down a column per 16-byte write: 8 x 8 (key run, d) lanes read 8
@@ -825,6 +971,28 @@ Plan attn_plan(int Lq, int Lk, int heads, int nseq, int W) {
   return p;
 }
 }  // namespace
+
+// Whether launch_flash_attn_small_bf16 takes these shapes: rounds of the chip
+// times keys.  Against the list kernel, through the entry point (us, list / small):
+// one round of 1500 keys 35.4 / 34.0, of 2000 39.9 / 40.8 (half a chip) and 44.7 /
+// 40.6 (all of it), of 3000 42.0 / 52.1, of 4000 47.8 / 62.9; two rounds of 200 keys
+// 31.8 / 25.6, of 512 37.6 / 33.4, of 1024 40.8 / 44.5.
+bool flash_attn_small_fits(int Lq, int Lk, int heads, int nseq, int n_cu) {
+  const int64_t rounds = ((int64_t)((Lq + 31) / 32) * heads * nseq + n_cu - 1) / n_cu;
+  return rounds * Lk <= SMALL_MAX_KEYS;
+}
+
+hipError_t launch_flash_attn_small_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v,
+                                        int64_t ldv, void* o, int64_t ldo, int Lq, int Lk, int heads,
+                                        bool bounded_logits, hipStream_t s, int split, int64_t gap, int nseq,
+                                        int64_t zs, int64_t gz) {
+  if (nseq < 1 || Lq < 1 || Lk < 1) return hipErrorInvalidValue;
+  const float scale_log2 = 1.4426950408889634f / sqrtf((float)D);
+  hipLaunchKernelGGL(bounded_logits ? flash_attn_small_kernel<true> : flash_attn_small_kernel<false>,
+                     dim3((Lq + 31) / 32, heads, nseq), dim3(512), 0, s, (const bf16_t*)q, ldq, (const bf16_t*)k, ldk,
+                     (const bf16_t*)v, ldv, (bf16_t*)o, ldo, Lq, Lk, scale_log2, SeqMap{split, gap, gz, zs});
+  return hipGetLastError();
+}
 
 size_t flash_attn_ws_bytes(int Lq, int Lk, int heads, int nseq, int n_cu) {
   const int W = attn_width(n_cu);

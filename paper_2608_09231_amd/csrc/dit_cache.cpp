@@ -297,13 +297,20 @@ dit_status ln_mod(dit_cache* c, const void* x, int64_t ldx, void* out, int64_t l
 
 // attention over joint rows: q,k,v inside Y (or separate), output into o;
 // nseq stacked sequences in one launch (bf16; see launch_flash_attn_bf16)
-// vt_ready: the transposed values are in vt_ws already
+// vt_ready: the transposed values are in vt_ws already (v_stored: those at v too)
 dit_status attention(dit_cache* c, const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v,
                      int64_t ldv, void* o, int64_t ldo, int Lq, int Lk, void* vt_ws, int split = 0x7fffffff,
-                     int64_t gap = 0, int nseq = 1, int64_t zs = 0, int64_t gz = 0, bool vt_ready = false) {
+                     int64_t gap = 0, int nseq = 1, int64_t zs = 0, int64_t gz = 0, bool vt_ready = false,
+                     bool v_stored = false) {
   const int heads = c->cfg.heads, hd = c->cfg.head_dim;
   const double flops = 4.0 * Lq * (double)Lk * heads * hd * nseq;
   if (c->bf16) {
+    if ((!vt_ready || v_stored) && dit::flash_attn_small_fits(Lq, Lk, heads, nseq, c->n_cu)) {
+      Scope s(c, DIT_K_ATTN, flops);
+      HIPCK(dit::launch_flash_attn_small_bf16(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, true, c->stream, split,
+                                              gap, nseq, zs, gz));
+      return DIT_OK;
+    }
     if (!vt_ready) {
       Scope s(c, DIT_K_FULL_OTHER, 2.0 * Lk * heads * hd * 2 * nseq);
       HIPCK(dit::launch_transpose_v_bf16(v, ldv, vt_ws, Lk, heads, c->stream, split, gap, nseq, zs, gz));
@@ -736,7 +743,7 @@ dit_status full_stack(dit_cache* c, const Seq& q, int t, int T) {
       const char* kv = sp(c, q.xkv, (size_t)i * xkv_elems(c));
       void* vt = c->bf16 ? (void*)((char*)q.xvt + (size_t)i * xvt_elems(c) * 2) : nullptr;
       TRY(attention(c, c->Y, ldY, kv, 2 * H, kv + (size_t)H * c->esz, 2 * H, sp(c, c->Y, 3 * H), ldY, N, Nt, vt,
-                    0x7fffffff, 0, 1, 0, 0, c->bf16));
+                    0x7fffffff, 0, 1, 0, 0, c->bf16, true));
       g = lin_args(c, sp(c, c->Y, 3 * H), ldY, w.xo, c->X, H, N, DIT_EPI_GATED_RES);
       g.gate = c->ones;
       TRY(gemm(c, &g, 1, cls));
@@ -1609,6 +1616,11 @@ dit_status attention_call(const void* q, int64_t ldq, const void* k, int64_t ldk
   hipGetDevice(&dev);
   hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   const bool bounded = (flags & DIT_ATTN_BOUNDED_LOGITS) != 0;
+  if (dit::flash_attn_small_fits(Lq, Lk, heads, 1, ncu)) {
+    HIPCK(dit::launch_flash_attn_small_bf16(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, bounded, s));
+    HIPCK(hipStreamSynchronize(s));
+    return DIT_OK;
+  }
   const PieceSlot ws(d, dit::flash_attn_ws_bytes(Lq, Lk, heads, 1, ncu));
   hipError_t e = dit::launch_transpose_v_bf16(v, ldv, vt, Lk, heads, s);
   if (e == hipSuccess)

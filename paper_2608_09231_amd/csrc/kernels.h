@@ -80,6 +80,12 @@ hipError_t launch_flash_attn_bf16(const void* q, int64_t ldq, const void* k, int
                                   int Lk, int heads, bool bounded_logits, hipStream_t s, int n_cu, float* ws,
                                   int split = 0x7fffffff, int64_t gap = 0, int nseq = 1, int64_t zs = 0,
                                   int64_t gz = 0);
+// The same for few, short sequences (flash_attn_small_fits), from v itself.
+bool flash_attn_small_fits(int Lq, int Lk, int heads, int nseq, int n_cu);
+hipError_t launch_flash_attn_small_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v,
+                                        int64_t ldv, void* o, int64_t ldo, int Lq, int Lk, int heads,
+                                        bool bounded_logits, hipStream_t s, int split = 0x7fffffff, int64_t gap = 0,
+                                        int nseq = 1, int64_t zs = 0, int64_t gz = 0);
 // Bytes of the workspace ws with which launch_flash_attn_bf16 shares the key
 // ranges of its last round out (0: it would not); without it (nullptr) every
 // work-group takes whole query blocks.

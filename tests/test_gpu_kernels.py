@@ -334,6 +334,7 @@ def bounded_case(torch, Lq, Lk, heads, bounded):
 @pytest.mark.parametrize("bounded", [True, False])
 @pytest.mark.parametrize("Lq,Lk,heads", [
     (1, 64 * 9, 1),       # one item, shared in two
+    (1, 64 * 30, 1),      # one item, shared in seven
     (257, 4100, 3),       # a ragged second query block, shares of one XCD in several pieces
     (8300, 700, 8),       # 33 items an XCD: a whole round and one shared item
     (8192, 130, 10),      # 40 an XCD, three tiles: whole items in the last round
@@ -349,6 +350,31 @@ def test_attention_last_round(Lq, Lk, heads, bounded):
     binding.attention_bf16(q, k, v, o, vt_ws=ws, **args)
     got = host_bf16(o)
     assert np.all(np.isfinite(got))
+    assert rel_l2(got[rows], ref) < 4e-3
+
+
+@pytest.mark.parametrize("bounded", [True, False])
+@pytest.mark.parametrize("Lq,Lk,heads", [
+    (1, 1, 1), (31, 31, 2), (33, 257, 3),   # waves without keys, one key past a block
+    (700, 1279, 2),                         # as many keys as the small kernel takes, uneven blocks
+    (3000, 95, 5),                          # two rounds of work-groups
+])
+def test_attention_small(Lq, Lk, heads, bounded):
+    """The kernel for few, short sequences against float64, NaN beyond the
+    last key and query (rows of the buffers that belong to someone else)."""
+    torch = torch_cuda()
+    (q, k, v), args, rows, ref = bounded_case(torch, Lq, Lk, heads, bounded)
+    H = heads * 128
+
+    def padded(t, n):  # a NaN row behind the last one
+        p = torch.full((n + 1, H), 0x7fc0, dtype=torch.int16, device="cuda")
+        p[:n] = t
+        return p
+    o = torch.full((Lq + 1, H), 0x7fc0, dtype=torch.int16, device="cuda")
+    ws = torch.zeros(H * ((Lk + 63) // 64 * 64), dtype=torch.int16, device="cuda")
+    binding.attention_bf16(padded(q, Lq), padded(k, Lk), padded(v, Lk), o, vt_ws=ws, **args)
+    got = host_bf16(o)
+    assert np.all(np.isnan(got[Lq])) and np.all(np.isfinite(got[:Lq]))
     assert rel_l2(got[rows], ref) < 4e-3
 
 
