@@ -977,7 +977,8 @@ Plan attn_plan(int Lq, int Lk, int heads, int nseq, int W) {
 // one round of 1500 keys 35.4 / 34.0, of 2000 39.9 / 40.8 (half a chip) and 44.7 /
 // 40.6 (all of it), of 3000 42.0 / 52.1, of 4000 47.8 / 62.9; two rounds of 200 keys
 // 31.8 / 25.6, of 512 37.6 / 33.4, of 1024 40.8 / 44.5.  More rounds pay the fixed
-// part of a work-group (query loads, 135 KB of LDS, the sum of the waves) each time.
+// part of a work-group (query loads, 135 KB of LDS, the sum of the waves) each time:
+// eight of 5 keys 27.4 / 34.3, twelve of 20 keys 35.1 / 45.1.
 bool flash_attn_small_fits(int Lq, int Lk, int heads, int nseq, int n_cu) {
   const int64_t rounds = ((int64_t)((Lq + 31) / 32) * heads * nseq + n_cu - 1) / n_cu;
   return rounds <= 2 && rounds * Lk <= SMALL_MAX_KEYS;
