@@ -158,6 +158,11 @@ __device__ __forceinline__ float sum_quarters(float v) {
   return over_quarters(v, [](float a, float b) { return a + b; });
 }
 
+// -m as the softmax's shift.  A query whose logits so far are all -inf
+// (overflow) has no maximum yet: exp2(-inf + 0) = 0 leaves its sums at zero,
+// where exp2(-inf + inf) would make them NaN for good.
+__device__ __forceinline__ float neg_shift(float m) { return m == -INFINITY ? 0.f : -m; }
+
 // 16 bytes per lane from base + off (bytes, valid up to `bytes`; zeros past
 // it) into LDS at dst + 16 lane.
 __device__ __forceinline__ void copy16(const void* base, uint32_t bytes, lds_void_t* dst, uint32_t off) {
@@ -357,8 +362,9 @@ __global__ __launch_bounds__(64 * NW) void flash_attn_kernel(
     if (__builtin_amdgcn_ballot_w64(need)) {
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
-        const float m_new = mx[g] > m_run[g] + RESCALE_SLACK ? mx[g] : m_run[g];
-        const float alpha = __builtin_amdgcn_exp2f(m_run[g] - m_new);
+        const bool up = mx[g] > m_run[g] + RESCALE_SLACK;
+        const float m_new = up ? mx[g] : m_run[g];
+        const float alpha = up ? __builtin_amdgcn_exp2f(m_run[g] - m_new) : 1.f;
         l_run[g] *= alpha;
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt)
@@ -376,7 +382,7 @@ __global__ __launch_bounds__(64 * NW) void flash_attn_kernel(
   };
   auto softmax_step = [&](int e, const f32x4_t (&sacc)[4][2], bf16x8_t (&pf)[2][2], Soft& x) {
     const int g = e >> 4, ks = (e >> 3) & 1, i = e & 7;
-    const float mneg = BOUNDED ? -BOUNDED_SHIFT_LOG2 : -m_run[g];
+    const float mneg = BOUNDED ? -BOUNDED_SHIFT_LOG2 : neg_shift(m_run[g]);
     const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[2 * ks + (i >> 2)][g][i & 3], scale_log2, mneg));
     if (!(e & 1)) {
       x.p0 = p;
@@ -744,11 +750,12 @@ __global__ __launch_bounds__(512) void flash_attn_small_kernel(
         }
         m[g] = mn;
       }
+      const float mneg = BOUNDED ? -BOUNDED_SHIFT_LOG2 : neg_shift(m[g]);
       uint32_t w[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 1][g][2 * (e & 1)], scale_log2, -m[g]));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 1][g][2 * (e & 1) + 1], scale_log2, -m[g]));
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 1][g][2 * (e & 1)], scale_log2, mneg));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 1][g][2 * (e & 1) + 1], scale_log2, mneg));
         w[e] = pack_bf16x2(p0, p1);
         l[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w[e]), ones, l[g], false);
       }

@@ -401,3 +401,39 @@ def test_attention_calls_in_flight():
     [t.start() for t in ts]
     [t.join() for t in ts]
     assert not errs, errs
+
+
+@pytest.mark.parametrize("Lq,Lk,heads,first", [
+    (40, 300, 2, 64),      # small kernel: whole 32-key blocks of a wave without a finite logit
+    (40, 300, 2, 0),       # the same from the first key on
+    (300, 3000, 2, 64),    # list kernel, last round shared: whole pieces without one
+    (300, 3000, 2, 0),     # the same, the first tiles of a piece included
+    (9000, 700, 8, 64),    # whole items: some of a wave's queries raise their maximum, others have none
+    (9000, 700, 8, 0),
+])
+def test_attention_overflowing_logits(Lq, Lk, heads, first):
+    """Logits that overflow to -inf weigh nothing: every second query against
+    the keys from `first` on, but for the last 70."""
+    torch = torch_cuda()
+    H = heads * 128
+    q = RNG.standard_normal((Lq, heads, 128))
+    k = RNG.standard_normal((Lk, heads, 128))
+    v = RNG.standard_normal((Lk, H))
+    huge = np.arange(Lk)
+    huge = (huge >= first) & (huge < Lk - 70)
+    q[:, :, 0] = 0.0
+    q[::2, :, 0] = 2e20
+    k[:, :, 0] = np.where(huge[:, None], -1e20, 0.0)
+    q_b, k_b, v_b = bf16_bits(q.reshape(Lq, H)), bf16_bits(k.reshape(Lk, H)), bf16_bits(v)
+    o = torch.full((Lq, H), 0x7fc0, dtype=torch.int16, device="cuda")
+    ws = torch.zeros(H * ((Lk + 63) // 64 * 64), dtype=torch.int16, device="cuda")
+    binding.attention_bf16(dev(torch, q_b), dev(torch, k_b), dev(torch, v_b), o, Lq=Lq, Lk=Lk, heads=heads, ldq=H,
+                           ldk=H, ldv=H, ldo=H, vt_ws=ws, flags=0)
+    got = host_bf16(o)
+    assert np.all(np.isfinite(got))
+    rows = np.unique(np.concatenate([[0, 1, Lq - 2, Lq - 1], RNG.choice(Lq, 24, replace=False)]))
+    for parity in (0, 1):
+        r = rows[rows % 2 == parity]
+        keys = ~huge if parity == 0 else np.ones(Lk, bool)
+        ref = round_bf16(dit.attention(bits_to_f64(q_b)[r], bits_to_f64(k_b)[keys], bits_to_f64(v_b)[keys], heads, 128))
+        assert rel_l2(got[r], ref) < 4e-3
