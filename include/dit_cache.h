@@ -187,7 +187,7 @@ dit_status dit_cache_sample_ex(dit_cache* h, float* latent, const void* text_emb
  * linear layer is one GEMM launch over all their rows, attention one launch
  * over all their sequences.  Sample j's result is the result of
  * dit_cache_sample_ex on its own inputs, up to the rounding of the stacked
- * launches.
+ * launches; its bits do not depend on what the other samples decide.
  *   latents   device, f32 [n_samples, n_img, in_channels]: x_0 in, x_T out
  *   text_emb  device, storage dtype [n_samples, batch, n_txt, ctx_dim]
  *   p         shared by all samples; p->forced_mask, if not NULL, is host

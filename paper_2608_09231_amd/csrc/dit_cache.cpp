@@ -103,7 +103,10 @@ struct dit_cache {
   // sample that computes) runs the block stack together, stream-major rows
   // [txt_0; ...; txt_{Q-1}; img_0; ...; img_{Q-1}] (see full_stack_multi)
   bool stacked = false;
-  bool several = false;  // the running call advances several samples
+  // the running call stacks several samples, any subset of which computes at a
+  // step: a sample's bits must not depend on the others' decisions, so no
+  // rule on the size of a stacked launch may pick another order of its sums
+  bool several = false;
 
   void* wdev = nullptr;
   size_t wbytes = 0;
@@ -261,7 +264,6 @@ GemmArgs lin_args(const dit_cache* c, const void* A, int64_t lda, const Lin& l, 
   g.A = A; g.lda = lda; g.W = l.w; g.ldw = l.in; g.bias = l.b;
   g.C = C; g.ldc = ldc; g.gate = nullptr;
   g.M = M; g.N = l.out; g.K = l.in; g.flags = flags;
-  g.one_chain = c->several;
   return g;
 }
 
@@ -305,7 +307,7 @@ dit_status attention(dit_cache* c, const void* q, int64_t ldq, const void* k, in
   const int heads = c->cfg.heads, hd = c->cfg.head_dim;
   const double flops = 4.0 * Lq * (double)Lk * heads * hd * nseq;
   if (c->bf16) {
-    if ((!vt_ready || v_stored) && dit::flash_attn_small_fits(Lq, Lk, heads, nseq, c->n_cu)) {
+    if (!c->several && (!vt_ready || v_stored) && dit::flash_attn_small_fits(Lq, Lk, heads, nseq, c->n_cu)) {
       Scope s(c, DIT_K_ATTN, flops);
       HIPCK(dit::launch_flash_attn_small_bf16(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, true, c->stream, split,
                                               gap, nseq, zs, gz));
@@ -318,7 +320,8 @@ dit_status attention(dit_cache* c, const void* q, int64_t ldq, const void* k, in
     Scope s(c, DIT_K_ATTN, flops);
     // q and k leave the projection through a unit-gain RMS norm: bounded logits
     HIPCK(dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt_ws, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads,
-                                      true, c->stream, c->n_cu, c->pieces, split, gap, nseq, zs, gz));
+                                      true, c->stream, c->n_cu, c->several ? nullptr : c->pieces, split, gap, nseq,
+                                      zs, gz));
   } else {
     if (nseq != 1) return fail(c, DIT_EINVAL, "f32 attention runs one sequence per launch");
     Scope s(c, DIT_K_ATTN, flops);
@@ -845,6 +848,11 @@ dit_status full_stack_multi(dit_cache* c, const Seq* seqs, int Q) {
   char* Ai = sp(c, c->A, (size_t)Lt * H);
   char* Yi = sp(c, c->Y, (size_t)Lt * ldY);
   const int cls = DIT_K_GEMM;
+  auto lin = [&](const void* A, int64_t lda, const Lin& l, void* C, int64_t ldc, int M, int flags = DIT_EPI_STORE) {
+    GemmArgs g = lin_args(c, A, lda, l, C, ldc, M, flags);
+    g.one_chain = c->several;
+    return g;
+  };
   for (int q = 0; q < Q; ++q) {
     HIPCK(hipMemcpyAsync(sp(c, c->X, (size_t)q * Nt * H), seqs[q].txt, (size_t)Nt * H * es,
                          hipMemcpyDeviceToDevice, c->stream));
@@ -920,7 +928,8 @@ dit_status full_stack_multi(dit_cache* c, const Seq* seqs, int Q) {
     g.vt_rows1 = rows1; g.vt_key1 = key1;
   };
   // one sequence: block 0's image-stream input is this step's indicator tensor m_t
-  const void* m0 = Q == 1 ? seqs[0].m0 : nullptr;
+  // (not where it is one of several: with others beside it the adaLN pass forms it)
+  const void* m0 = Q == 1 && !c->several ? seqs[0].m0 : nullptr;
   for (int i = 0; i < c->cfg.n_double; ++i) {
     const DoubleW& w = c->M.dbl[i];
     const size_t mi = (size_t)12 * H * i, mt = mi + 6 * H;  // image / text stream chunks
@@ -929,8 +938,8 @@ dit_status full_stack_multi(dit_cache* c, const Seq* seqs, int Q) {
                            mr.base + mt + H, DIT_K_FULL_OTHER));
     else TRY(lnm(mt, mi));
     GemmArgs g[2];
-    g[0] = lin_args(c, use_m0 ? m0 : (const void*)Ai, H, w.qkv[0], Yi, ldY, Li);
-    g[1] = lin_args(c, c->A, H, w.qkv[1], c->Y, ldY, Lt);
+    g[0] = lin(use_m0 ? m0 : (const void*)Ai, H, w.qkv[0], Yi, ldY, Li);
+    g[1] = lin(c->A, H, w.qkv[1], c->Y, ldY, Lt);
     g[0].rms_cols = g[1].rms_cols = 2 * H;
     with_vt(g[0], N, Nt);   // image rows: keys Nt .. Nt + N - 1 of sequence m / N
     with_vt(g[1], Nt, 0);   // text rows: keys 0 .. Nt - 1 of sequence m / Nt
@@ -938,23 +947,23 @@ dit_status full_stack_multi(dit_cache* c, const Seq* seqs, int Q) {
     if (!vt_fused) g[0].vt = g[1].vt = nullptr;
     TRY(gemm(c, g, 2, cls));
     TRY(attn(vt_fused));
-    TRY(gated(lin_args(c, Yi + 3 * H * es, ldY, w.o[0], Xi, H, Li, DIT_EPI_GATED_RES),
-              lin_args(c, sp(c, c->Y, 3 * H), ldY, w.o[1], c->X, H, Lt, DIT_EPI_GATED_RES), mi + 2 * H,
+    TRY(gated(lin(Yi + 3 * H * es, ldY, w.o[0], Xi, H, Li, DIT_EPI_GATED_RES),
+              lin(sp(c, c->Y, 3 * H), ldY, w.o[1], c->X, H, Lt, DIT_EPI_GATED_RES), mi + 2 * H,
               mt + 2 * H));
     TRY(lnm(mt + 3 * H, mi + 3 * H));
-    g[0] = lin_args(c, Ai, H, w.mlp0[0], Yi + 4 * H * es, ldY, Li);
-    g[1] = lin_args(c, c->A, H, w.mlp0[1], sp(c, c->Y, 4 * H), ldY, Lt);
+    g[0] = lin(Ai, H, w.mlp0[0], Yi + 4 * H * es, ldY, Li);
+    g[1] = lin(c->A, H, w.mlp0[1], sp(c, c->Y, 4 * H), ldY, Lt);
     g[0].gelu_from = g[1].gelu_from = 0;
     TRY(gemm(c, g, 2, cls));
-    TRY(gated(lin_args(c, Yi + 4 * H * es, ldY, w.mlp1[0], Xi, H, Li, DIT_EPI_GATED_RES),
-              lin_args(c, sp(c, c->Y, 4 * H), ldY, w.mlp1[1], c->X, H, Lt, DIT_EPI_GATED_RES), mi + 5 * H,
+    TRY(gated(lin(Yi + 4 * H * es, ldY, w.mlp1[0], Xi, H, Li, DIT_EPI_GATED_RES),
+              lin(sp(c, c->Y, 4 * H), ldY, w.mlp1[1], c->X, H, Lt, DIT_EPI_GATED_RES), mi + 5 * H,
               mt + 5 * H));
   }
   for (int i = 0; i < c->cfg.n_single; ++i) {
     const SingleW& w = c->M.sgl[i];
     const size_t ms = (size_t)12 * H * c->cfg.n_double + (size_t)3 * H * i;
     TRY(lnm(ms, ms));
-    GemmArgs g = lin_args(c, c->A, H, w.l1, c->Y, ldY, LL);
+    GemmArgs g = lin(c->A, H, w.l1, c->Y, ldY, LL);
     g.rms_cols = 2 * H;
     g.gelu_from = 3 * H;
     g.gap_at = 3 * H;
@@ -965,12 +974,12 @@ dit_status full_stack_multi(dit_cache* c, const Seq* seqs, int Q) {
     TRY(gemm(c, &g, 1, cls));
     TRY(attn(vt_fused));
     if (mr.d == 0) {
-      g = lin_args(c, sp(c, c->Y, 3 * H), ldY, w.l2, c->X, H, LL, DIT_EPI_GATED_RES);
+      g = lin(sp(c, c->Y, 3 * H), ldY, w.l2, c->X, H, LL, DIT_EPI_GATED_RES);
       g.gate = mr.base + ms + 2 * H;
       TRY(gemm(c, &g, 1, cls));
     } else {
-      TRY(gated(lin_args(c, Yi + 3 * H * es, ldY, w.l2, Xi, H, Li, DIT_EPI_GATED_RES),
-                lin_args(c, sp(c, c->Y, 3 * H), ldY, w.l2, c->X, H, Lt, DIT_EPI_GATED_RES), ms + 2 * H,
+      TRY(gated(lin(Yi + 3 * H * es, ldY, w.l2, Xi, H, Li, DIT_EPI_GATED_RES),
+                lin(sp(c, c->Y, 3 * H), ldY, w.l2, c->X, H, Lt, DIT_EPI_GATED_RES), ms + 2 * H,
                 ms + 2 * H));
     }
   }
@@ -1191,9 +1200,8 @@ dit_status run_batch(dit_cache* c, int S, float* latents, const void* text_emb, 
   }
   TRY(ensure_lanes(c, S));
   TRY(ensure_T(c, T, S));
-  c->several = false;  // what is formed once per sample has the same shapes for any S
+  c->several = c->stacked && S > 1;
   TRY(prepare(c, S, text_emb, sig, T));
-  c->several = S > 1;
 
   const bool pair = nb == 2;
   const bool unipc = p.solver == DIT_SOLVER_UNIPC;

@@ -1216,6 +1216,8 @@ Prob make_prob(const GemmArgs& g, int bm, int bn) {
 int ring_parts(long tiles, const GemmArgs* g, int n, int n_cu) {
   const long rem = tiles % n_cu;
   if (tiles < n_cu || rem == 0) return 0;
+  for (int i = 0; i < n; ++i)
+    if (g[i].one_chain) return 0;
   int nk = g[0].K / 64;
   for (int i = 1; i < n; ++i) nk = std::min(nk, g[i].K / 64);
   const int parts = (int)std::min<long>(n_cu / rem, nk / 4);

@@ -25,8 +25,9 @@ struct GemmArgs {
   int gseg = 0;
   int64_t gstride = 0;
   // Every output's products are added in one chain over K whatever the number
-  // of rows (bf16): the stacked launches of several samples then give a
-  // sample the same bits however many share the launch.
+  // of rows (bf16: neither the small-tile kernel nor a last round shared out
+  // over K): the stacked launches of several samples then give a sample the
+  // same bits however many share the launch.
   bool one_chain = false;
   // f32 only: the result goes into the Euler update euler_x[m][n] +=
   // euler_alpha (acc + bias) (row stride ldc) instead of C.

@@ -130,6 +130,37 @@ def test_batch_sizes_on_one_handle():
         np.testing.assert_array_equal(s2[j].sums[1:2], s3[j].sums[1:2])
 
 
+# Prompt 0 computes at t = 0 and t = 1; beside it at t = 1: all, two, one and none of the others.
+NEIGHBOURS = [np.array([[1, 1, 0]] * (1 + k) + [[1, 0, 1]] * (3 - k), np.uint8) for k in (3, 2, 1, 0)]
+
+
+@pytest.mark.parametrize("dims", [
+    # small kernels' sizes, ragged rows and keys
+    dict(heads=2, mlp_hidden=1024, n_img=200, n_txt=40, n_double=2, n_single=2),
+    # 272 tiles of 256 x 256 and K = 5120 where four compute: a last round that one prompt would share out
+    dict(heads=8, mlp_hidden=4096, n_img=4096, n_txt=256, n_double=0, n_single=1),
+])
+@pytest.mark.parametrize("pooled", [1, 0])
+def test_batch_bits_do_not_depend_on_neighbours(monkeypatch, dims, pooled):
+    """A prompt's latent and indicator sums are the same bits whatever the
+    other prompts of the call decide at each step."""
+    torch = torch_cuda()
+    cfg = synth.ModelConfig(name="case", dtype="bf16", n_cross=0, hidden=128 * dims["heads"], head_dim=128,
+                            in_channels=64, ctx_dim=96, batch=1, pooled_text=pooled, **dims)
+    monkeypatch.setitem(synth.WORKLOADS, "case", synth.Workload("case", cfg, T=3, B=2, shift=3.0, guidance=1.0, seed=41))
+    w = synth.workload("case")
+    weights, x0, text, gate = inputs(w, 4)
+    h = binding.DitCache(cfg, weights.blob)
+    try:
+        runs = [run_batch(torch, h, w, x0, text, gate, 3, 2, forced_masks=m) for m in NEIGHBOURS]
+    finally:
+        h.close()
+    x, s = runs[0]
+    for xn, sn in runs[1:]:
+        np.testing.assert_array_equal(xn[0], x[0])
+        np.testing.assert_array_equal(sn[0].sums[1:], s[0].sums[1:])
+
+
 def test_batch_error_paths():
     torch = torch_cuda()
     w = synth.workload("small_bf16")
