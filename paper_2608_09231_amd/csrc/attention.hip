@@ -1003,10 +1003,11 @@ hipError_t launch_flash_attn_small_bf16(const void* q, int64_t ldq, const void* 
   return hipGetLastError();
 }
 
-size_t flash_attn_ws_bytes(int Lq, int Lk, int heads, int nseq, int n_cu) {
-  const int W = attn_width(n_cu);
-  return attn_plan(Lq, Lk, heads, nseq, W).shares ? (size_t)16 * W * PIECE_FLOATS * sizeof(float) : 0;
+bool flash_attn_uses_ws(int Lq, int Lk, int heads, int nseq, int n_cu) {
+  return attn_plan(Lq, Lk, heads, nseq, attn_width(n_cu)).shares > 0;
 }
+
+size_t flash_attn_ws_bytes(int n_cu) { return (size_t)16 * attn_width(n_cu) * PIECE_FLOATS * sizeof(float); }
 
 hipError_t launch_flash_attn_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk,
                                   const void* vt, int ldvt, void* o, int64_t ldo, int Lq, int Lk,

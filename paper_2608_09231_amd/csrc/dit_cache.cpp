@@ -122,10 +122,9 @@ struct dit_cache {
   void* Y = nullptr;       // [cap_seq L, 4H+F]: q | k | v | attn out | mlp hidden
   void* vt = nullptr;      // bf16 [cap_seq, heads, 128, round_up(L, 64)]
   float* modq = nullptr;   // f32 [cap_seq, n_mod]: gathered modulation vectors of one step
-  // f32 pieces of work shared out in a launch's last round (flash_attn_ws_bytes,
-  // gemm_bf16_ws_bytes), or nullptr: one launch at a time on the stream
+  // f32 pieces of work shared out in a launch's last round (65 MiB; one launch at
+  // a time on the stream), from the first launch on whose shape asks for them
   float* pieces = nullptr;
-  size_t pieces_bytes = 0;
   void* yf = nullptr;      // [N, H] final-layer input
   float* vel = nullptr;    // f32 [nb, N, C]
   float* ones = nullptr;   // f32 [H] (ungated residual)
@@ -267,16 +266,39 @@ GemmArgs lin_args(const dit_cache* c, const void* A, int64_t lda, const Lin& l, 
   return g;
 }
 
+template <typename P>
+dit_status dalloc(dit_cache* c, P** p, size_t bytes) {
+  void* q = nullptr;
+  if (bytes == 0) bytes = 16;
+  hipError_t e = hipMalloc(&q, bytes);
+  if (e != hipSuccess) return fail(c, DIT_ENOMEM, "hipMalloc(" + std::to_string(bytes) + ") failed");
+  *p = (P*)q;
+  return DIT_OK;
+}
+
+// Whether a launch is shared out is decided by its shape alone, so that the
+// results do not depend on what the handle ran before.
+dit_status ensure_pieces(dit_cache* c, bool uses) {
+  if (!uses || c->pieces) return DIT_OK;
+  return dalloc(c, &c->pieces, std::max(dit::flash_attn_ws_bytes(c->n_cu), dit::gemm_bf16_ws_bytes(c->n_cu)));
+}
+
+// A linear layer's launch in the storage type (f32: with the per-head norm).
+dit_status launch_gemm(dit_cache* c, const GemmArgs* g, int n) {
+  if (c->bf16) {
+    TRY(ensure_pieces(c, dit::gemm_bf16_uses_ws(g, n, c->n_cu)));
+    HIPCK(dit::launch_gemm_bf16(g, n, c->stream, c->n_cu, c->pieces));
+  } else {
+    HIPCK(dit::launch_gemm_f32(g, n, c->cfg.head_dim, c->n_cu, c->stream));
+  }
+  return DIT_OK;
+}
+
 dit_status gemm(dit_cache* c, GemmArgs* g, int n, int cls) {
   double flops = 0;
   for (int i = 0; i < n; ++i) flops += 2.0 * g[i].M * (double)g[i].N * g[i].K;
   Scope sc(c, cls, flops);
-  if (c->bf16) {
-    HIPCK(dit::launch_gemm_bf16(g, n, c->stream, c->n_cu, c->pieces));
-  } else {
-    HIPCK(dit::launch_gemm_f32(g, n, c->cfg.head_dim, c->n_cu, c->stream));  // with the per-head norm
-  }
-  return DIT_OK;
+  return launch_gemm(c, g, n);
 }
 
 template <typename Fn>
@@ -317,11 +339,13 @@ dit_status attention(dit_cache* c, const void* q, int64_t ldq, const void* k, in
       Scope s(c, DIT_K_FULL_OTHER, 2.0 * Lk * heads * hd * 2 * nseq);
       HIPCK(dit::launch_transpose_v_bf16(v, ldv, vt_ws, Lk, heads, c->stream, split, gap, nseq, zs, gz));
     }
+    const bool share = !c->several && dit::flash_attn_uses_ws(Lq, Lk, heads, nseq, c->n_cu);
+    TRY(ensure_pieces(c, share));
     Scope s(c, DIT_K_ATTN, flops);
     // q and k leave the projection through a unit-gain RMS norm: bounded logits
     HIPCK(dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt_ws, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads,
-                                      true, c->stream, c->n_cu, c->several ? nullptr : c->pieces, split, gap, nseq,
-                                      zs, gz));
+                                      true, c->stream, c->n_cu, share ? c->pieces : nullptr, split, gap, nseq, zs,
+                                      gz));
   } else {
     if (nseq != 1) return fail(c, DIT_EINVAL, "f32 attention runs one sequence per launch");
     Scope s(c, DIT_K_ATTN, flops);
@@ -405,16 +429,6 @@ dit_status validate(const dit_model_config* g, std::string& why) {
   return DIT_OK;
 }
 
-template <typename P>
-dit_status dalloc(dit_cache* c, P** p, size_t bytes) {
-  void* q = nullptr;
-  if (bytes == 0) bytes = 16;
-  hipError_t e = hipMalloc(&q, bytes);
-  if (e != hipSuccess) return fail(c, DIT_ENOMEM, "hipMalloc(" + std::to_string(bytes) + ") failed");
-  *p = (P*)q;
-  return DIT_OK;
-}
-
 // LN statistics matrix of the patch embedding for the column-sliced step
 // kernel, from the host weight blob (W_in, b_in still blob offsets).
 dit_status upload_stream_stats(dit_cache* c, const uint16_t* blob) {
@@ -481,21 +495,6 @@ dit_status ensure_seq(dit_cache* c, int Q) {
     HIPCK(hipMemsetAsync(c->vt, 0, vb, c->stream));
   }
   if (c->stacked && c->cfg.pooled_text) TRY(dalloc(c, &c->modq, (size_t)Q * c->n_mod * 4));
-  if (c->bf16) {  // any subset of the sequences may compute
-    const int heads = c->cfg.heads;
-    size_t need = c->cfg.n_cross ? dit::flash_attn_ws_bytes(c->N, c->Nt, heads, 1, c->n_cu) : 0;
-    for (int n = 1; n <= Q; ++n) need = std::max(need, dit::flash_attn_ws_bytes(c->L, c->L, heads, n, c->n_cu));
-    // the widest layer fills the chip with 256 x 256 tiles: some launch may end in a round of few
-    if (rup(LB, 256) / 256 * (rup(std::max(c->F, 3 * c->H), 256) / 256) >= (size_t)c->n_cu)
-      need = std::max(need, dit::gemm_bf16_ws_bytes(c->n_cu));
-    if (need > c->pieces_bytes) {
-      if (c->pieces) hipFree(c->pieces);
-      c->pieces = nullptr;
-      c->pieces_bytes = 0;
-      TRY(dalloc(c, &c->pieces, need));
-      c->pieces_bytes = need;
-    }
-  }
   c->cap_seq = Q;
   return DIT_OK;
 }
@@ -728,7 +727,7 @@ dit_status full_stack(dit_cache* c, const Seq& q, int t, int T) {
         g.vt_ld = (int)rup(N, 64);
         g.vt_rows0 = N;
         g.vt_key0 = 0;
-        vt_fused = dit::gemm_bf16_fuses_vt(&g, 1, c->n_cu, c->pieces != nullptr);
+        vt_fused = dit::gemm_bf16_fuses_vt(&g, 1, c->n_cu);
         if (!vt_fused) g.vt = nullptr;
       }
       TRY(gemm(c, &g, 1, cls));
@@ -943,7 +942,7 @@ dit_status full_stack_multi(dit_cache* c, const Seq* seqs, int Q) {
     g[0].rms_cols = g[1].rms_cols = 2 * H;
     with_vt(g[0], N, Nt);   // image rows: keys Nt .. Nt + N - 1 of sequence m / N
     with_vt(g[1], Nt, 0);   // text rows: keys 0 .. Nt - 1 of sequence m / Nt
-    const bool vt_fused = dit::gemm_bf16_fuses_vt(g, 2, c->n_cu, c->pieces != nullptr);
+    const bool vt_fused = dit::gemm_bf16_fuses_vt(g, 2, c->n_cu);
     if (!vt_fused) g[0].vt = g[1].vt = nullptr;
     TRY(gemm(c, g, 2, cls));
     TRY(attn(vt_fused));
@@ -969,7 +968,7 @@ dit_status full_stack_multi(dit_cache* c, const Seq* seqs, int Q) {
     g.gap_at = 3 * H;
     g.gap = H;
     with_vt(g, Nt, 0, Lt, N, Nt);  // the Q text row blocks, then the Q image row blocks
-    const bool vt_fused = dit::gemm_bf16_fuses_vt(&g, 1, c->n_cu, c->pieces != nullptr);
+    const bool vt_fused = dit::gemm_bf16_fuses_vt(&g, 1, c->n_cu);
     if (!vt_fused) g.vt = nullptr;
     TRY(gemm(c, &g, 1, cls));
     TRY(attn(vt_fused));
@@ -1007,14 +1006,11 @@ dit_status final_project(dit_cache* c, int b, int cls, float* latent = nullptr, 
     return DIT_OK;
   }
   GemmArgs g = lin_args(c, c->yf, H, c->M.fin, c->vel + (size_t)b * N * c->C, c->C, N, DIT_EPI_F32);
-  if (c->bf16) {
-    HIPCK(dit::launch_gemm_bf16(&g, 1, c->stream, c->n_cu, c->pieces));
-  } else {
-    g.euler_x = latent;  // f32: the Euler update in the epilogue
+  if (!c->bf16) {  // f32: the Euler update in the epilogue
+    g.euler_x = latent;
     g.euler_alpha = dsig;
-    HIPCK(dit::launch_gemm_f32(&g, 1, c->cfg.head_dim, c->n_cu, c->stream));
   }
-  return DIT_OK;
+  return launch_gemm(c, &g, 1);
 }
 
 // full step: y = S(LN(h_out)(1+scale_f)+shift_f), then the projection
@@ -1309,13 +1305,11 @@ dit_status run_batch(dit_cache* c, int S, float* latents, const void* text_emb, 
       } else {
         Scope sc(c, DIT_K_INDICATOR, (double)NH * c->esz * (t == 0 ? 2 : (l.i_prev == l.i_last ? 3 : 4)));
         GemmArgs g = lin_args(c, lat(j), C, c->M.img_in, l.h, H, N);
-        if (c->bf16) {
+        if (c->bf16) {  // (f32: the latent is stored in S already)
           HIPCK(dit::launch_cast_from_f32<bf16_t>(lat(j), (bf16_t*)c->xs, (int64_t)NC, c->stream));
           g.A = c->xs;
-          HIPCK(dit::launch_gemm_bf16(&g, 1, c->stream, c->n_cu, c->pieces));
-        } else {  // the latent is stored in S already
-          HIPCK(dit::launch_gemm_f32(&g, 1, c->cfg.head_dim, c->n_cu, c->stream));
         }
+        TRY(launch_gemm(c, &g, 1));
         TRY(typed(c, [&](auto* tp) {
           using Ty = std::remove_pointer_t<decltype(tp)>;
           return dit::launch_indicator<Ty>((const Ty*)l.h, (Ty*)l.mbuf[l.i_new], (const Ty*)mp, (const Ty*)ml, N,
@@ -1629,7 +1623,7 @@ dit_status attention_call(const void* q, int64_t ldq, const void* k, int64_t ldk
     HIPCK(hipStreamSynchronize(s));
     return DIT_OK;
   }
-  const PieceSlot ws(d, dit::flash_attn_ws_bytes(Lq, Lk, heads, 1, ncu));
+  const PieceSlot ws(d, dit::flash_attn_uses_ws(Lq, Lk, heads, 1, ncu) ? dit::flash_attn_ws_bytes(ncu) : 0);
   hipError_t e = dit::launch_transpose_v_bf16(v, ldv, vt, Lk, heads, s);
   if (e == hipSuccess)
     e = dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads, bounded, s, ncu,

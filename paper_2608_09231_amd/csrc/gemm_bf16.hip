@@ -1357,9 +1357,9 @@ static bool vt_ok(const GemmArgs* g, int n, int c) {
   return true;
 }
 
-bool gemm_bf16_fuses_vt(const GemmArgs* g, int n, int n_cu, bool ws) {
+bool gemm_bf16_fuses_vt(const GemmArgs* g, int n, int n_cu) {
   if (n < 1 || n > 2) return false;
-  return vt_ok(g, n, pick_cfg(g, n, n_cu, ws));
+  return vt_ok(g, n, pick_cfg(g, n, n_cu, true));
 }
 
 bool gemm_bf16_uses_ws(const GemmArgs* g, int n, int n_cu) {

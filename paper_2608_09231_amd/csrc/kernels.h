@@ -49,15 +49,17 @@ struct GemmArgs {
 // bf16 MFMA GEMM; n = 1 or 2 independent problems in one launch.  Invalid
 // arguments (no tile configuration admits the problem) return an error.
 // ws: workspace of gemm_bf16_ws_bytes, with which a last round of few tiles is
-// shared out over K, or nullptr.
+// shared out over K where gemm_bf16_uses_ws, or nullptr (whole tiles then).  A
+// launch that would not use it runs the same with or without.
 hipError_t launch_gemm_bf16(const GemmArgs* g, int n, hipStream_t s, int n_cu, float* ws);
 size_t gemm_bf16_ws_bytes(int n_cu);
-bool gemm_bf16_uses_ws(const GemmArgs* g, int n, int n_cu);  // whether the launch would
+bool gemm_bf16_uses_ws(const GemmArgs* g, int n, int n_cu);
 // Whether launch_gemm_bf16 can write the transposed values of these problems
 // itself (the vt fields set): 128-column head groups, 32-row aligned segments
 // and the 256 x 256 kernel.  Otherwise the caller leaves vt unset and
-// transposes the values with launch_transpose_v_bf16.
-bool gemm_bf16_fuses_vt(const GemmArgs* g, int n, int n_cu, bool ws);
+// transposes the values with launch_transpose_v_bf16.  (For a launch that gets
+// ws where it uses one.)
+bool gemm_bf16_fuses_vt(const GemmArgs* g, int n, int n_cu);
 // v = A W^T + bias for N <= 128 (multiple of 16), K % 32 == 0, f32 output; with
 // x != nullptr the result goes into the Euler update x += alpha * v instead.
 hipError_t launch_proj_small_n(const void* A, int64_t lda, const void* W, int64_t ldw, const void* bias,
@@ -87,10 +89,11 @@ hipError_t launch_flash_attn_small_bf16(const void* q, int64_t ldq, const void* 
                                         int64_t ldv, void* o, int64_t ldo, int Lq, int Lk, int heads,
                                         bool bounded_logits, hipStream_t s, int split = 0x7fffffff, int64_t gap = 0,
                                         int nseq = 1, int64_t zs = 0, int64_t gz = 0);
-// Bytes of the workspace ws with which launch_flash_attn_bf16 shares the key
-// ranges of its last round out (0: it would not); without it (nullptr) every
-// work-group takes whole query blocks.
-size_t flash_attn_ws_bytes(int Lq, int Lk, int heads, int nseq, int n_cu);
+// ws: workspace of flash_attn_ws_bytes, with which launch_flash_attn_bf16 shares
+// the key ranges of its last round out where flash_attn_uses_ws; without it
+// (nullptr) every work-group takes whole query blocks.
+bool flash_attn_uses_ws(int Lq, int Lk, int heads, int nseq, int n_cu);
+size_t flash_attn_ws_bytes(int n_cu);
 // f32 attention, head_dim <= 128 (multiple of 4).
 hipError_t launch_attn_f32(const float* q, int64_t ldq, const float* k, int64_t ldk,
                            const float* v, int64_t ldv, float* o, int64_t ldo, int Lq, int Lk,

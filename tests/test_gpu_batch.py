@@ -130,6 +130,26 @@ def test_batch_sizes_on_one_handle():
         np.testing.assert_array_equal(s2[j].sums[1:2], s3[j].sums[1:2])
 
 
+def test_shared_last_round_on_one_handle(monkeypatch):
+    """The same where a lone prompt's widest layer (three tile rows of 87)
+    is shared out over K and nothing else of the model is."""
+    torch = torch_cuda()
+    cfg = synth.ModelConfig(name="case", dtype="bf16", n_double=0, n_single=1, n_cross=0, hidden=2304, heads=18,
+                            head_dim=128, mlp_hidden=15360, in_channels=64, ctx_dim=96, n_img=520, n_txt=80)
+    monkeypatch.setitem(synth.WORKLOADS, "case", synth.Workload("case", cfg, T=2, B=1, shift=3.0, guidance=1.0, seed=43))
+    w = synth.workload("case")
+    weights, x0, text, gate = inputs(w, 2)
+    h = binding.DitCache(cfg, weights.blob)
+    try:
+        x1, s1 = run_one(torch, h, w, x0[0], text[0], gate, w.T, w.B)
+        run_batch(torch, h, w, x0, text, gate, w.T, w.B)
+        x1b, s1b = run_one(torch, h, w, x0[0], text[0], gate, w.T, w.B)
+    finally:
+        h.close()
+    np.testing.assert_array_equal(x1, x1b)
+    np.testing.assert_array_equal(s1.sums[1:], s1b.sums[1:])
+
+
 # Prompt 0 computes at t = 0 and t = 1; beside it at t = 1: all, two, one and none of the others.
 NEIGHBOURS = [np.array([[1, 1, 0]] * (1 + k) + [[1, 0, 1]] * (3 - k), np.uint8) for k in (3, 2, 1, 0)]
 
