@@ -131,11 +131,12 @@ def test_batch_sizes_on_one_handle():
 
 
 def test_shared_last_round_on_one_handle(monkeypatch):
-    """The same where a lone prompt's widest layer (three tile rows of 87)
-    is shared out over K and nothing else of the model is."""
+    """The same where a lone prompt's widest layer (four tile rows of 91, 108
+    tiles past the whole round in two shares of K) is shared out and nothing
+    else of the model is."""
     torch = torch_cuda()
-    cfg = synth.ModelConfig(name="case", dtype="bf16", n_double=0, n_single=1, n_cross=0, hidden=2304, heads=18,
-                            head_dim=128, mlp_hidden=15360, in_channels=64, ctx_dim=96, n_img=520, n_txt=80)
+    cfg = synth.ModelConfig(name="case", dtype="bf16", n_double=0, n_single=1, n_cross=0, hidden=3328, heads=26,
+                            head_dim=128, mlp_hidden=13312, in_channels=64, ctx_dim=96, n_img=720, n_txt=80)
     monkeypatch.setitem(synth.WORKLOADS, "case", synth.Workload("case", cfg, T=2, B=1, shift=3.0, guidance=1.0, seed=43))
     w = synth.workload("case")
     weights, x0, text, gate = inputs(w, 2)
