@@ -193,6 +193,8 @@ dit_status dit_cache_sample_ex(dit_cache* h, float* latent, const void* text_emb
  *   p         shared by all samples; p->forced_mask, if not NULL, is host
  *             [n_samples, T] (one replay mask per sample)
  *   out       host array of n_samples schedules, one per sample
+ * (A handle whose launches leave few tiles for the chip's last round takes
+ * 65 MiB more at the first such launch, see dit_kernels.h, and keeps them.)
  * Workspace for n_samples is allocated on first use and kept (per sample
  * about 6 [n_img, hidden] tensors plus, for the stacked block stack, the
  * rows of every sequence).  On error every latent is unspecified and each

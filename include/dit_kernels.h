@@ -42,6 +42,13 @@ enum {
  *   gap_at, gap  output column = n + gap for n >= gap_at (writes the MLP
  *             half of a fused projection next to a hole for the attention
  *             output); gap = 0 = none
+ * Where few 256 x 256 output tiles are left past the chip's last whole round,
+ * they are shared out over K and the parts added from f32 sums in device
+ * memory of the library: 65 MiB per call in flight that does so, allocated on
+ * first use, at most four such buffers per GPU kept for further calls.  Whether
+ * a call does depends on its shape alone, so that the result's bits do not
+ * depend on other calls; only with no device memory left does it run whole
+ * tiles instead (the same result up to the rounding of f32 sums).
  * Errors: DIT_EINVAL (null pointers, bad flags), DIT_ESHAPE (K % 8, lda or
  * ldw < K, ldc too small, gap < 0, rms_cols not a multiple of 128), DIT_EHIP. */
 typedef struct dit_gemm_desc {
@@ -72,11 +79,11 @@ enum {
  * ldq), k and v [Lk, heads*128] (ldk, ldv), o [Lq, heads*128] (ldo);
  * head h occupies columns [128h, 128h + 128).  flags: 0 or
  * DIT_ATTN_BOUNDED_LOGITS.  vt_ws is a device workspace of heads * 128 *
- * round_up(Lk, 64) bf16 elements for v transposed per head.  Where
- * the work fills the chip's CUs only partly in its last round, the key ranges
- * are shared out and the parts added from f32 sums in device memory of the
- * library; with more than two such calls in flight on one GPU the further ones
- * run unshared (the same result up to the rounding of f32 sums).
+ * round_up(Lk, 64) bf16 elements for v transposed per head.  Where the work
+ * fills the chip's CUs only partly in its last round, the key ranges are
+ * shared out and the parts added from f32 sums in device memory of the library
+ * (see dit_gemm_bf16): by the shapes alone, so that the result's bits do not
+ * depend on other calls.
  * Errors: DIT_EINVAL, DIT_ESHAPE (Lq, Lk < 1), DIT_EHIP. */
 dit_status dit_attention_bf16(const void* q, int64_t ldq, const void* k, int64_t ldk,
                               const void* v, int64_t ldv, void* o, int64_t ldo,
@@ -89,13 +96,14 @@ dit_status dit_attention_bf16(const void* q, int64_t ldq, const void* k, int64_t
 
 /* dit_attention_bf16 without the vt_ws workspace argument, for callers that
  * cannot allocate device memory (code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc).  The transposed values go to a
- * fixed device array of DIT_NOALLOC_VT_MAX_ELEMS bf16 elements inside the
- * library, one per GPU, held until the process ends; the call allocates
- * nothing (no hipMalloc / hipFree, no allocating library routine).  The
- * array's device address is looked up once per device, on the first call
- * made with that device current.  Same arguments, kernels and result bits
- * as dit_attention_bf16.  Every call on one GPU shares that GPU's array:
+ * loops, harnesses that forbid hipMalloc).  The transposed values and the f32
+ * sums of a shared last round go to fixed device arrays inside the library
+ * (DIT_NOALLOC_VT_MAX_ELEMS bf16 elements, 32 MiB, and 65 MiB), one of each per
+ * GPU, held until the process ends; the call allocates nothing (no hipMalloc /
+ * hipFree, no allocating library routine).  The arrays' device addresses are
+ * looked up once per device, on the first call made with that device
+ * current.  Same arguments, kernels and result bits as dit_attention_bf16.
+ * Every call on one GPU shares that GPU's arrays:
  * calls that overlap on one GPU (other streams or host threads) race and
  * must be serialised by the caller.  Errors: as dit_attention_bf16, plus
  * DIT_ESHAPE when heads * 128 * round_up(Lk, 64) > DIT_NOALLOC_VT_MAX_ELEMS

@@ -1528,29 +1528,28 @@ dit_status run_batch(dit_cache* c, int S, float* latents, const void* text_emb, 
 }  // namespace
 
 // ------------------------------------------------------- components' scratch
-// Device memory of the component entry points, which allocate nothing:
-// transposed values of dit_attention_bf16_noalloc, and the f32 pieces of work
-// shared out in a launch's last round.  In host code these names are host-side
-// stand-ins, not device memory: kernels take the addresses that
-// hipGetSymbolAddress returns for the current device.
+// Device memory of dit_attention_bf16_noalloc, which allocates nothing: the
+// transposed values, and the f32 pieces of a shared last round.  Its callers
+// serialise it.  In host code these names are host-side stand-ins, not device
+// memory: kernels take the addresses that hipGetSymbolAddress returns for the
+// current device.
+constexpr size_t kPieceBytes = (size_t)65 << 20;  // flash_attn_ws_bytes, gemm_bf16_ws_bytes of 256 CUs (65, 64 MiB)
 static __device__ __align__(256) uint16_t scratch[DIT_NOALLOC_VT_MAX_ELEMS];
-namespace {
-constexpr int kPieceSlots = 2;                     // calls in flight on one GPU that may share work out
-constexpr size_t kPieceBytes = (size_t)66 << 20;   // flash_attn_ws_bytes, gemm_bf16_ws_bytes of 256 CUs (65, 64 MiB)
-}  // namespace
-static __device__ __align__(256) unsigned char pieces[kPieceSlots * kPieceBytes];
+static __device__ __align__(256) unsigned char pieces[kPieceBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
+constexpr int kIdlePieces = 4;  // buffers kept per GPU for further calls (260 MiB at most)
 std::mutex g_scratch_mu;
 struct DeviceScratch {
-  void* vt = nullptr;
-  char* pieces = nullptr;
-  bool used[kPieceSlots] = {};
+  void* vt = nullptr;      // the arrays above
+  float* pieces = nullptr;
+  void* idle[kIdlePieces] = {};
+  int n_idle = 0;
 } g_scratch[kMaxDevices];
 
 // The current device's copies of the arrays, looked up once per device.
-dit_status device_scratch(DeviceScratch** out) {
+dit_status static_scratch(void** vt, float** pc) {
   dit_cache* c = nullptr;
   int dev = -1;
   HIPCK(hipGetDevice(&dev));
@@ -1558,77 +1557,105 @@ dit_status device_scratch(DeviceScratch** out) {
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   DeviceScratch& d = g_scratch[dev];
   if (!d.vt) {
-    void *vt = nullptr, *pc = nullptr;
-    HIPCK(hipGetSymbolAddress(&vt, HIP_SYMBOL(scratch)));
-    HIPCK(hipGetSymbolAddress(&pc, HIP_SYMBOL(pieces)));
-    if (!vt || !pc) return fail(c, DIT_EHIP, "hipGetSymbolAddress returned no address");
-    d.pieces = (char*)pc;
-    d.vt = vt;
+    void *v = nullptr, *p = nullptr;
+    HIPCK(hipGetSymbolAddress(&v, HIP_SYMBOL(scratch)));
+    HIPCK(hipGetSymbolAddress(&p, HIP_SYMBOL(pieces)));
+    if (!v || !p) return fail(c, DIT_EHIP, "hipGetSymbolAddress returned no address");
+    d.pieces = (float*)p;
+    d.vt = v;
   }
-  *out = &d;
+  *vt = d.vt;
+  *pc = d.pieces;
   return DIT_OK;
 }
 
-// A slot of the piece array for the time of one call (the calls return after
-// their stream has drained).  With every slot taken by calls of other threads
-// the launch runs without one: whole query blocks or tiles only, the same
-// result up to the rounding of the sums.
-struct PieceSlot {
-  DeviceScratch* d;
-  int slot = -1;
-  PieceSlot(DeviceScratch* d_, size_t bytes) : d(d_) {
-    if (bytes == 0 || bytes > kPieceBytes) return;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    for (int i = 0; i < kPieceSlots && slot < 0; ++i)
-      if (!d->used[i]) {
-        d->used[i] = true;
-        slot = i;
+int current_cus() {
+  int dev = 0, ncu = 256;
+  hipGetDevice(&dev);
+  hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  return ncu;
+}
+
+// A buffer of kPieceBytes for the time of one call (the calls return after
+// their stream has drained): each call in flight has its own, so that whether
+// a launch is shared out depends on its shape and not on other threads.  Up to
+// kIdlePieces stay for further calls.  get() is nullptr where the launch uses
+// none, or where the device has no memory left (the launch then runs whole).
+struct PieceBuffer {
+  int dev = -1;
+  void* p = nullptr;
+  explicit PieceBuffer(bool uses) {
+    if (!uses || hipGetDevice(&dev) != hipSuccess) return;
+    if (dev >= 0 && dev < kMaxDevices) {
+      std::lock_guard<std::mutex> lock(g_scratch_mu);
+      DeviceScratch& d = g_scratch[dev];
+      if (d.n_idle) p = d.idle[--d.n_idle];
+    }
+    if (p) return;
+    const Relaxed r;
+    if (hipMalloc(&p, kPieceBytes) != hipSuccess) {
+      p = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  ~PieceBuffer() {
+    if (!p) return;
+    if (dev >= 0 && dev < kMaxDevices) {
+      std::lock_guard<std::mutex> lock(g_scratch_mu);
+      DeviceScratch& d = g_scratch[dev];
+      if (d.n_idle < kIdlePieces) {
+        d.idle[d.n_idle++] = p;
+        return;
       }
+    }
+    const Relaxed r;
+    (void)hipFree(p);
   }
-  ~PieceSlot() {
-    if (slot < 0) return;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    d->used[slot] = false;
-  }
-  PieceSlot(const PieceSlot&) = delete;
-  PieceSlot& operator=(const PieceSlot&) = delete;
-  float* get() const { return slot < 0 ? nullptr : (float*)(d->pieces + slot * kPieceBytes); }
+  PieceBuffer(const PieceBuffer&) = delete;
+  PieceBuffer& operator=(const PieceBuffer&) = delete;
+  float* get() const { return (float*)p; }
+
+ private:
+  // An allocation is no part of a capture that another thread may be at.
+  struct Relaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  };
 };
 
 dit_status gemm_call(const GemmArgs& g, hipStream_t s) {
   dit_cache* c = nullptr;
-  int dev = 0, ncu = 256;
-  hipGetDevice(&dev);
-  hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  DeviceScratch* d = nullptr;
-  TRY(device_scratch(&d));
-  const PieceSlot ws(d, dit::gemm_bf16_uses_ws(&g, 1, ncu) ? dit::gemm_bf16_ws_bytes(ncu) : 0);
+  const int ncu = current_cus();
+  const PieceBuffer ws(dit::gemm_bf16_ws_bytes(ncu) <= kPieceBytes && dit::gemm_bf16_uses_ws(&g, 1, ncu));
   const hipError_t e = dit::launch_gemm_bf16(&g, 1, s, ncu, ws.get());
-  const hipError_t done = hipStreamSynchronize(s);  // the slot is free only after it
+  const hipError_t done = hipStreamSynchronize(s);  // the buffer is free only after it
   HIPCK(e);
   HIPCK(done);
   return DIT_OK;
 }
 
+bool attention_shares(int Lq, int Lk, int heads) {
+  const int ncu = current_cus();
+  return !dit::flash_attn_small_fits(Lq, Lk, heads, 1, ncu) && dit::flash_attn_ws_bytes(ncu) <= kPieceBytes &&
+         dit::flash_attn_uses_ws(Lq, Lk, heads, 1, ncu);
+}
+
+// ws: kPieceBytes, used where attention_shares; or nullptr
 dit_status attention_call(const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v, int64_t ldv, void* o,
-                          int64_t ldo, int Lq, int Lk, int heads, int flags, void* vt, DeviceScratch* d,
-                          hipStream_t s) {
+                          int64_t ldo, int Lq, int Lk, int heads, int flags, void* vt, float* ws, hipStream_t s) {
   dit_cache* c = nullptr;
-  int dev = 0, ncu = 256;
-  hipGetDevice(&dev);
-  hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  const int ncu = current_cus();
   const bool bounded = (flags & DIT_ATTN_BOUNDED_LOGITS) != 0;
+  hipError_t e;
   if (dit::flash_attn_small_fits(Lq, Lk, heads, 1, ncu)) {
-    HIPCK(dit::launch_flash_attn_small_bf16(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, bounded, s));
-    HIPCK(hipStreamSynchronize(s));
-    return DIT_OK;
+    e = dit::launch_flash_attn_small_bf16(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, bounded, s);
+  } else {
+    e = dit::launch_transpose_v_bf16(v, ldv, vt, Lk, heads, s);
+    if (e == hipSuccess)
+      e = dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads, bounded, s, ncu, ws);
   }
-  const PieceSlot ws(d, dit::flash_attn_uses_ws(Lq, Lk, heads, 1, ncu) ? dit::flash_attn_ws_bytes(ncu) : 0);
-  hipError_t e = dit::launch_transpose_v_bf16(v, ldv, vt, Lk, heads, s);
-  if (e == hipSuccess)
-    e = dit::launch_flash_attn_bf16(q, ldq, k, ldk, vt, (int)rup(Lk, 64), o, ldo, Lq, Lk, heads, bounded, s, ncu,
-                                    ws.get());
-  const hipError_t done = hipStreamSynchronize(s);  // the slot is free only after it
+  const hipError_t done = hipStreamSynchronize(s);  // ws is free only after it
   HIPCK(e);
   HIPCK(done);
   return DIT_OK;
@@ -1841,9 +1868,9 @@ extern "C" dit_status dit_attention_bf16(const void* q, int64_t ldq, const void*
                                          int32_t flags, void* vt_ws, void* hip_stream) {
   if (!vt_ws) return fail(nullptr, DIT_EINVAL, "null argument");
   TRY(check_attention(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, flags));
-  DeviceScratch* d = nullptr;
-  TRY(device_scratch(&d));
-  return attention_call(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, flags, vt_ws, d, (hipStream_t)hip_stream);
+  const PieceBuffer ws(attention_shares(Lq, Lk, heads));
+  return attention_call(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, flags, vt_ws, ws.get(),
+                        (hipStream_t)hip_stream);
 }
 
 extern "C" dit_status dit_attention_bf16_noalloc(const void* q, int64_t ldq, const void* k, int64_t ldk,
@@ -1855,7 +1882,9 @@ extern "C" dit_status dit_attention_bf16_noalloc(const void* q, int64_t ldq, con
     return fail(nullptr, DIT_ESHAPE, "heads * 128 * round_up(Lk, 64) = " + std::to_string(need) +
                                          " exceeds the allocation-free limit of " +
                                          std::to_string((size_t)DIT_NOALLOC_VT_MAX_ELEMS) + " elements");
-  DeviceScratch* d = nullptr;
-  TRY(device_scratch(&d));
-  return attention_call(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, flags, d->vt, d, (hipStream_t)hip_stream);
+  void* vt = nullptr;
+  float* ws = nullptr;
+  TRY(static_scratch(&vt, &ws));
+  return attention_call(q, ldq, k, ldk, v, ldv, o, ldo, Lq, Lk, heads, flags, vt,
+                        attention_shares(Lq, Lk, heads) ? ws : nullptr, (hipStream_t)hip_stream);
 }

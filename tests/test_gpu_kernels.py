@@ -379,8 +379,8 @@ def test_attention_small(Lq, Lk, heads, bounded):
 
 
 def test_attention_calls_in_flight():
-    """Four threads with streams of their own: two calls hold the shared
-    items' memory, further ones run unshared; all within the same bar."""
+    """Four threads with streams of their own, each call with memory of its
+    own for the shared items."""
     import threading
     torch = torch_cuda()
     cases, errs = [bounded_case(torch, 600, 3000, 2, True) for _ in range(4)], []
@@ -437,3 +437,39 @@ def test_attention_overflowing_logits(Lq, Lk, heads, first):
         keys = ~huge if parity == 0 else np.ones(Lk, bool)
         ref = round_bf16(dit.attention(bits_to_f64(q_b)[r], bits_to_f64(k_b)[keys], bits_to_f64(v_b)[keys], heads, 128))
         assert rel_l2(got[r], ref) < 4e-3
+
+
+def test_component_bits_do_not_depend_on_calls_in_flight():
+    """Two calls wait behind other work on their streams; a third on a stream
+    of its own gives the bits of a lone call (all of them share out their last
+    round, attention and GEMM alike)."""
+    import threading
+    import time
+    torch = torch_cuda()
+    (q, k, v), args, _, _ = bounded_case(torch, 1000, 3000, 2, True)
+    ws = [torch.zeros(256 * 3008, dtype=torch.int16, device="cuda") for _ in range(3)]
+    M, N, K = 4300, 4104, 2112
+    a, w, b = [dev(torch, make(s, 0.1)[0]) for s in ((M, K), (N, K), (N,))]
+    big = torch.randn(8192, 8192, device="cuda").bfloat16()
+
+    def attention(i, out, stream):
+        binding.attention_bf16(q, k, v, out, vt_ws=ws[i], stream=stream, **args)
+
+    def gemm(i, out, stream):
+        binding.gemm_bf16(a, w, b, out, M=M, N=N, K=K, stream=stream)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for call, shape in ((attention, (1000, 256)), (gemm, (M, N))):
+        alone, *outs = [torch.zeros(shape, dtype=torch.int16, device="cuda") for _ in range(4)]
+        torch.cuda.synchronize()
+        call(2, alone, streams[2])
+        for s in streams[:2]:
+            with torch.cuda.stream(s):
+                for _ in range(100):
+                    big @ big
+        ts = [threading.Thread(target=call, args=(i, outs[i], streams[i])) for i in range(2)]
+        [t.start() for t in ts]
+        time.sleep(0.03)
+        call(2, outs[2], streams[2])
+        [t.join() for t in ts]
+        for o in outs:
+            assert torch.equal(o, alone)
