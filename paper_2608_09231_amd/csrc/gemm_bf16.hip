@@ -457,6 +457,20 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+// vmcnt(N) and lgkmcnt(0) in one wait (same encoding as wait_vmcnt).
+template <int N>
+__device__ __forceinline__ void wait_vmcnt_lgkm0() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
+}
+
+// Workgroup barrier without the workgroup-scope fence of __syncthreads: that
+// fence waits for every outstanding global load of the wave, copies to LDS
+// included, which would drain the copies a deeper pipeline keeps in flight.
+// The memory clobber keeps the compiler from moving memory operations across
+// it; callers wait for their own LDS reads and copies first.
+__device__ __forceinline__ void barrier_no_fence() { asm volatile("s_barrier" ::: "memory"); }
+
 // 16 bytes per lane from base + voff + soff (bytes, 32-bit offsets) into LDS
 // at dst + 16 lane: a raw buffer load with an LDS destination.  Offsets past
 // 4 GiB - 1 read zeros; the host admits this path only when every row of
@@ -625,10 +639,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(Batch b) 
     if (s < nk) issue(s);
 
   for (int kt = 0; kt < nk; ++kt) {
-    // slice kt must have landed: later slices may stay in flight
-    if (nk - 1 - kt >= STAGES - 2) wait_vmcnt<(STAGES - 2) * INS>();
+    // slice kt must have landed (later slices may stay in flight) and this
+    // wave's reads of slice kt-1 have returned
+    if (nk - 1 - kt >= STAGES - 2) wait_vmcnt_lgkm0<(STAGES - 2) * INS>();
     else __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();  // every wave's copies of slice kt are in; slice kt-1 is no longer read
+    // then every wave's copies of slice kt are in and slice kt-1 is no longer
+    // read.  (__syncthreads would drain the copies in flight: through the entry
+    // point 28 x 18432 x 3072 59.4 us, so 43.7; 512 x 3072 x 4096 50.9, 45.5; 64 x
+    // 16384 x 1024 32.1, 26.5; at 28 x 52224 x 3072 both are at 81, 4 TB/s.)
+    barrier_no_fence();
     if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1);
     const char* sA = smem + (kt % STAGES) * STAGE;
     const char* sB = sA + BM * BK_ * 2;
@@ -662,20 +681,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(Batch b) 
     epilogue<TM, TN, WM, WN>(P, acc, m0, n0, wm, wn, lrow, lhalf);
   }
 }
-
-// vmcnt(N) and lgkmcnt(0) in one wait (same encoding as wait_vmcnt).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt_lgkm0() {
-  static_assert(N >= 0 && N < 64, "vmcnt");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
-}
-
-// Workgroup barrier without the workgroup-scope fence of __syncthreads: that
-// fence waits for every outstanding global load of the wave, copies to LDS
-// included, which would drain the copies a deeper pipeline keeps in flight.
-// The memory clobber keeps the compiler from moving memory operations across
-// it; callers wait for their own LDS reads and copies first.
-__device__ __forceinline__ void barrier_no_fence() { asm volatile("s_barrier" ::: "memory"); }
 
 // Transposed values straight from the accumulators of a wave that owns 64
 // rows x one 128-column head group (4 x 8 blocks of 16 x 16).  In a block,
@@ -757,7 +762,7 @@ constexpr int PIECE_WAVE = 64 * 128;  // floats of a wave's part of a piece, in 
 // Requires K % 64 == 0, K >= 128 and the LDS-staged epilogue's conditions.
 template <int KIND>
 __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(Batch b) {
-  constexpr int BM = 256, BN = 256, BK_ = 64, WGN = 2;
+  constexpr int BK_ = 64, WGN = 2;
   constexpr int WM = 64, WN = 128, TM = 4, TN = 8;
   constexpr int UNIT = 256 * BK_ * 2;  // one operand slice
   constexpr int INS = 4;                // 1 KB copies per wave per operand slice
