@@ -151,6 +151,30 @@ def test_shared_last_round_on_one_handle(monkeypatch):
     np.testing.assert_array_equal(s1.sums[1:], s1b.sums[1:])
 
 
+def test_shared_last_round_of_a_pair(monkeypatch):
+    """A guidance pair's gated layers in shares of K against the same pair in
+    a call over two prompts, which runs whole tiles: the rows that the shares
+    hold by themselves (a gate vector of the other branch there moves them by
+    2e-2 in the first gated layer and 7e-2 in the second, from the oracle)."""
+    from tests.test_gpu_sampler import SHARED_PAIR
+    torch = torch_cuda()
+    cfg = synth.ModelConfig(name="case", dtype="bf16", n_cross=0, head_dim=128, in_channels=64, ctx_dim=96, batch=2,
+                            **SHARED_PAIR)
+    monkeypatch.setitem(synth.WORKLOADS, "case", synth.Workload("case", cfg, T=2, B=1, shift=3.0, guidance=4.0, seed=37))
+    w = synth.workload("case")
+    weights, x0, text, gate = inputs(w, 2)
+    h = binding.DitCache(cfg, weights.blob)
+    try:
+        x1, _ = run_one(torch, h, w, x0[0], text[0], gate, 2, 1)
+        x2, _ = run_batch(torch, h, w, x0, text, gate, 2, 1)
+    finally:
+        h.close()
+    assert not np.array_equal(x1, x2[0])
+    print("pair, shared against whole:", rel_l2(x1, x2[0]), rel_l2(x1[-512:], x2[0][-512:]))
+    assert rel_l2(x1[-512:], x2[0][-512:]) <= SELF_TOL["bf16"]
+    assert rel_l2(x1, x2[0]) <= SELF_TOL["bf16"]
+
+
 # Prompt 0 computes at t = 0 and t = 1; beside it at t = 1: all, two, one and none of the others.
 NEIGHBOURS = [np.array([[1, 1, 0]] * (1 + k) + [[1, 0, 1]] * (3 - k), np.uint8) for k in (3, 2, 1, 0)]
 

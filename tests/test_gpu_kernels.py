@@ -176,12 +176,16 @@ def test_gemm_few_rows(M, N, K, flags):
     assert_bf16_close(host_bf16(out), round_bf16(y))
 
 
-@pytest.mark.parametrize("M,N,K,flags", [
+LAST_ROUND_GEMMS = [
     (4300, 4104, 2112, binding.EPI_STORE),       # 289 tiles: 33 shared out in 7 uneven parts of 33 slices
     (4300, 4104, 2112, binding.EPI_GATED_RES),
-    (4100, 4360, 1600, binding.EPI_F32),         # 306 tiles: 50 in 5
+    (4100, 4360, 2112, binding.EPI_F32),         # 306 tiles: 50 in 5
+    (4100, 4360, 2112, binding.EPI_SILU),
     (4096, 6144, 4096, binding.EPI_STORE),       # 384 tiles: 128 in 2
-])
+]
+
+
+@pytest.mark.parametrize("M,N,K,flags", [(4100, 4360, 1600, binding.EPI_F32)] + LAST_ROUND_GEMMS)  # (first: whole tiles)
 def test_gemm_ring_last_round(M, N, K, flags):
     """Tiles past the last whole round in shares of K, added by the finishing
     kernel with the ring kernel's epilogues (norm, GELU and column gap too):
@@ -199,6 +203,8 @@ def test_gemm_ring_last_round(M, N, K, flags):
         args.update(rms_cols=2048, gelu_from=3072, gap_at=3072, gap=gap)
         ref = np.concatenate([dit.rms_heads(y[:, :2048], 16, 128), y[:, 2048:3072],
                               np.zeros((len(rows), gap)), dit.gelu_tanh(y[:, 3072:])], axis=1)
+    elif flags == binding.EPI_SILU:
+        ref = dit.silu(y)
     else:
         ref = y
     gate = None
@@ -331,15 +337,21 @@ def bounded_case(torch, Lq, Lk, heads, bounded):
     return [dev(torch, t) for t in (q_b, k_b, v_b)], args, rows, ref
 
 
+LAST_ROUND_ATTENTION = [  # Lq, Lk, heads, whole rounds before it, shares that hold parts of two items (None: not shared)
+    (1, 64 * 30, 1, 0, False),    # one item, shared in seven
+    (256, 768, 40, 0, False),     # items in three shares each, the fewest that a shared item has
+    (257, 4100, 3, 0, False),     # a ragged second query block, shares of one XCD in several pieces
+    (5000, 2001, 8, 0, True),     # 20 items an XCD in 32 shares, ragged queries and keys
+    (9300, 750, 8, 1, False),     # a whole round, then five items in fifteen
+    (13200, 2001, 8, 1, True),    # a whole round, then 20 items in 32
+    (8300, 700, 8, 1, None),      # 33 items an XCD, eleven tiles: a whole round, one whole item
+    (8192, 130, 10, 1, None),     # 40 an XCD, three tiles: whole items in the last round
+    (2048, 2050, 1, 0, False),    # eight items, a last tile of two keys
+]
+
+
 @pytest.mark.parametrize("bounded", [True, False])
-@pytest.mark.parametrize("Lq,Lk,heads", [
-    (1, 64 * 9, 1),       # one item, shared in two
-    (1, 64 * 30, 1),      # one item, shared in seven
-    (257, 4100, 3),       # a ragged second query block, shares of one XCD in several pieces
-    (8300, 700, 8),       # 33 items an XCD: a whole round and one shared item
-    (8192, 130, 10),      # 40 an XCD, three tiles: whole items in the last round
-    (2048, 2050, 1),      # eight items, a last tile of two keys
-])
+@pytest.mark.parametrize("Lq,Lk,heads", [(1, 64 * 9, 1)] + [c[:3] for c in LAST_ROUND_ATTENTION])  # (first: small kernel)
 def test_attention_last_round(Lq, Lk, heads, bounded):
     """Items per work-group, the shared last round and its pieces, ragged
     queries and keys: sampled rows against float64."""
@@ -353,12 +365,15 @@ def test_attention_last_round(Lq, Lk, heads, bounded):
     assert rel_l2(got[rows], ref) < 4e-3
 
 
-@pytest.mark.parametrize("bounded", [True, False])
-@pytest.mark.parametrize("Lq,Lk,heads", [
+SMALL_ATTENTION = [
     (1, 1, 1), (31, 31, 2), (33, 257, 3),   # waves without keys, one key past a block
     (700, 1279, 2),                         # as many keys as the small kernel takes, uneven blocks
     (3000, 95, 5),                          # two rounds of work-groups
-])
+]
+
+
+@pytest.mark.parametrize("bounded", [True, False])
+@pytest.mark.parametrize("Lq,Lk,heads", SMALL_ATTENTION)
 def test_attention_small(Lq, Lk, heads, bounded):
     """The kernel for few, short sequences against float64, NaN beyond the
     last key and query (rows of the buffers that belong to someone else)."""

@@ -100,6 +100,24 @@ def test_f32_layer_shapes(monkeypatch, heads, hd, F, C, ctx, N, Nt):
     parity("case")
 
 
+# a guidance pair whose gated layers (image and text rows in one launch, a gate vector per branch) end in a shared
+# last round: 288 tiles of 256 x 256, 32 of them in eight shares of K each, the second branch's last 512 image rows
+# and the text rows
+SHARED_PAIR = dict(n_double=1, n_single=0, hidden=2048, heads=16, mlp_hidden=2048, n_img=4352, n_txt=256)
+# one whose key tiles lie on both sides of the text rows' end (not a multiple of 64), too many keys for the small
+# attention kernel, its last round shared
+STRADDLING_PAIR = dict(n_double=1, n_single=1, hidden=256, heads=2, mlp_hidden=1024, n_img=1400, n_txt=77)
+
+
+@pytest.mark.parametrize("dims", [SHARED_PAIR, STRADDLING_PAIR])
+def test_bf16_pair_shapes(monkeypatch, dims):
+    cfg = synth.ModelConfig(name="case", dtype="bf16", n_cross=0, head_dim=128, in_channels=64, ctx_dim=96, batch=2,
+                            **dims)
+    monkeypatch.setitem(synth.WORKLOADS, "case",
+                        synth.Workload("case", cfg, T=2, B=1, shift=3.0, guidance=4.0, seed=37))
+    parity("case")
+
+
 def test_small_bf16_parity():
     sched, ores, err = parity("small_bf16")
     print("small_bf16 rel-L2", err, "schedule", sched.full.tolist())
