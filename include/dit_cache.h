@@ -64,7 +64,7 @@ enum { DIT_INDICATOR_MODULATED = 0, DIT_INDICATOR_PATCH = 1 };
  * blocks: self-attention, cross-attention to the text, FFN).
  * Requirements: hidden = heads * head_dim; bf16 needs head_dim == 128 and
  * hidden, mlp_hidden, ctx_dim, in_channels, time_dim multiples of 8; f32
- * needs head_dim <= 128 and a multiple of 4. */
+ * needs head_dim 16, 32, 64 or 128. */
 typedef struct dit_model_config {
   int32_t abi_version;   /* DIT_ABI_VERSION                                  */
   int32_t dtype;         /* storage dtype S: DIT_DTYPE_F32 or DIT_DTYPE_BF16  */

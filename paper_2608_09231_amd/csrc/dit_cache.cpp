@@ -1002,7 +1002,7 @@ dit_status final_project(dit_cache* c, int b, int cls, float* latent = nullptr, 
   Scope sc(c, cls, 0);
   if (proj_fits(c)) {
     HIPCK(dit::launch_proj_small_n(c->yf, H, c->M.fin.w, H, c->M.fin.b, c->vel + (size_t)b * N * c->C, c->C,
-                                   latent, c->C, dsig, N, c->C, H, c->stream));
+                                   latent, c->C, dsig, N, c->C, H, c->n_cu, c->stream));
     return DIT_OK;
   }
   GemmArgs g = lin_args(c, c->yf, H, c->M.fin, c->vel + (size_t)b * N * c->C, c->C, N, DIT_EPI_F32);

@@ -1210,14 +1210,21 @@ Prob make_prob(const GemmArgs& g, int bm, int bn) {
 }
 
 // Shares of K for the tiles of a ring launch past the last whole round (0:
-// they stay whole).  Where they fill at most half the chip, the shares take
-// nk / parts slices (1.2 us each) instead of nk; writing, adding and the
-// second launch cost about 20 us.  Through the entry point, whole tiles (or the
-// 128 x 128 ones chosen instead) against shares: 6144 x 3072 x 15360 gated (288
-// tiles) 724 -> 429 us, 6144 x 3072 x 3072 154 -> 123, 16896 x 3072 x 12288 (792)
-// 1145 -> 941, 6144 x 4096 x 8192 (384, two shares) 407 -> 323; 16896 x 9216 x
-// 3072 (2376 tiles, 3 shares of 16 slices) no change.  Past half the chip the
-// pieces (256 KB each, written and read) outweigh the idle CUs.
+// they stay whole).  Where they fill at most half the chip, floor(n_cu / rest)
+// shares take nk / parts slices (1.2 us each with every CU busy) instead of nk;
+// writing, adding and the second launch cost about 20 us.  (Past half the chip
+// that is one share: nothing to share.)  Through the entry point, whole tiles
+// (or the 128 x 128 ones chosen instead) against shares, us:
+//   one whole round: 6144 x 3072 x 15360 (288 tiles) 724 / 429, 6144 x 3072 x 3072
+//     161 / 130, 6144 x 4096 x 3072 (384, two shares, 24 slices saved) 174 / 151,
+//     4352 x 4096 x 1792 (272, 24 saved) 105 / 89; below 24: 6144 x 4096 x 2560 (20)
+//     151 / 151 and 4352 x 4096 x 1280 (16) 86 / 86, but 4352 x 4096 x 1600 (21) 97 / 83
+//   two or three, many shares: 16640 x 2048 x 2048 (520, 28 saved) 159 / 147, 16896 x
+//     3072 x 2048 (792, 28) 222 / 208
+//   three or more, two or three shares: the idle CUs' power goes to the others,
+//     so a slice saved is worth less: K = 3072 at 864 tiles 310 / 308, 1152 388 / 396,
+//     2376 756 / 762; K = 4096 395 / 390, 497 / 494, 965 / 957; K = 5120 481 / 468, 613 /
+//     604, 1193 / 1179
 int ring_parts(long tiles, const GemmArgs* g, int n, int n_cu) {
   const long rem = tiles % n_cu;
   if (tiles < n_cu || rem == 0) return 0;
@@ -1226,7 +1233,8 @@ int ring_parts(long tiles, const GemmArgs* g, int n, int n_cu) {
   int nk = g[0].K / 64;
   for (int i = 1; i < n; ++i) nk = std::min(nk, g[i].K / 64);
   const int parts = (int)std::min<long>(n_cu / rem, nk / 4);
-  return parts >= 2 && nk - nk / parts >= SPLIT_MIN_SLICES ? parts : 0;
+  if (parts < 2 || nk - nk / parts < SPLIT_MIN_SLICES) return 0;
+  return tiles / n_cu >= 3 && parts <= 3 && nk < 64 ? 0 : parts;
 }
 
 int pick_cfg(const GemmArgs* g, int n, int n_cu, bool ws) {
@@ -1298,10 +1306,10 @@ int pick_cfg(const GemmArgs* g, int n, int n_cu, bool ws) {
 
 hipError_t launch_proj_small_n(const void* A, int64_t lda, const void* W, int64_t ldw, const void* bias,
                                float* out, int64_t ldo, float* x, int64_t ldx, float alpha, int M, int N,
-                               int K, hipStream_t s) {
+                               int K, int n_cu, hipStream_t s) {
   if (K % 32 || N % 16 || N > 128 || M < 1) return hipErrorInvalidValue;
   // 32 rows a work-group where those still give every CU two of them
-  const bool two = M >= 32 * 512;
+  const bool two = M >= 32 * 2 * n_cu;
   const dim3 grid((M + (two ? 31 : 15)) / (two ? 32 : 16));
 #define DIT_PROJ(NT_)                                                                                  \
   case NT_:                                                                                            \

@@ -8,6 +8,8 @@
 // idle.  Measured on the 80 x 896 x 128 (with the RMS norm) and 80 x 128 x 640
 // layers of the 64 + 16 token workload against 64 x 64 tiles with 16-deep LDS
 // slices: 25.9 + 4.1 (the norm's own launch) -> 5.8 us and 54.9 -> 7.5 us.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -76,7 +78,9 @@ __global__ __launch_bounds__(64 * waves_of(TS)) void gemm_f32_kernel(BatchF b) {
     wr[i] = p.W + (int64_t)min(n0 + nw + 16 * i + lr, p.N - 1) * p.ldw;
   }
   f32x4_t acc[NB][NB] = {};
-  constexpr int U = 5;  // steps whose loads are in flight together (K = 640 in one go)
+  // steps whose loads are in flight together: 3 against 5 the same below a few
+  // hundred 32 x 32 tiles, 1152 x 1536 x 256 21.3 / 24.3 us, 1152 x 3072 x 1280 156 / 178
+  constexpr int U = 3;
   for (int s = s0; s < s1; s += U) {
     f32x4_t a[U][NB], w[U][NB];
 #pragma unroll
@@ -166,6 +170,7 @@ hipError_t launch_gemm_f32(const GemmArgs* g, int n, int head_dim, int n_cu, hip
   if (n < 1 || n > 2) return hipErrorInvalidValue;
   BatchF b;
   int64_t tiles64 = 0, tiles32 = 0;
+  int K = g[0].K;
   bool vec = true, rms = false;
   for (int i = 0; i < n; ++i) {
     const GemmArgs& a = g[i];
@@ -173,11 +178,21 @@ hipError_t launch_gemm_f32(const GemmArgs* g, int n, int head_dim, int n_cu, hip
     tiles32 += (int64_t)((a.M + 31) / 32) * ((a.N + 31) / 32);
     vec &= a.K % 4 == 0 && a.lda % 4 == 0 && a.ldw % 4 == 0 && !(((uintptr_t)a.A | (uintptr_t)a.W) & 15);
     rms |= a.rms_cols > 0;
+    K = std::min(K, a.K);
   }
-  // 64 x 64 tiles halve the operand reads; below two per CU the shared K of
-  // the small tiles is faster.  A handful of 32 x 32 tiles is bound by what
-  // one CU can load: a quarter of the tile each then.
-  const int ts = tiles64 >= 2 * n_cu ? 64 : tiles32 * 8 > n_cu ? 32 : 16;
+  // Per launch, us (M x N x K without the norm):
+  // - 16 x 16 tiles while they make about one round of the chip (a 32 x 32 tile is
+  //   bound by what one CU can load): against 32 x 32, 12 tiles of 32 x 32 (80 x 128 x
+  //   640) 6.1 / 9.7, 76 (600 x 128 x 640) 8.7 / 9.8, 72 (80 x 768 x 1280) 8.8 / 15.7;
+  //   144 (1152 x 128 x 640) 11.5 / 9.8, 152 (600 x 256 x 640) 11.6 / 10.0.  With the norm
+  //   of 32-wide heads they need its launch (1.9 us) beside: from K = 640 on.
+  // - 64 x 64 (half the operand reads, K not shared) where they make one round and
+  //   32 x 32 four: against 32 x 32, 216 tiles (1152 x 768) K = 256 18.1 / 13.9, 640
+  //   29.0 / 30.5, 1280 47 / 56, 3072 95 / 121; 192 (240 x 3072 x 1280) 46 / 41, 480 (600 x
+  //   3072 x 1280) 113 / 101, 864 (1152 x 3072) K = 256 55 / 45, 1280 223 / 178 (five
+  //   steps' loads in flight).
+  const bool few = 10 * tiles32 <= 3 * n_cu && !(rms && head_dim == 32 && K < 640);
+  const int ts = few ? 16 : tiles64 <= n_cu && tiles32 > 3 * n_cu && K >= 640 ? 64 : 32;
   const int hd = rms && ts % head_dim == 0 ? head_dim : 0;
   int total = 0;
   for (int i = 0; i < n; ++i) {

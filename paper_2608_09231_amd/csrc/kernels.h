@@ -64,8 +64,10 @@ bool gemm_bf16_fuses_vt(const GemmArgs* g, int n, int n_cu);
 // x != nullptr the result goes into the Euler update x += alpha * v instead.
 hipError_t launch_proj_small_n(const void* A, int64_t lda, const void* W, int64_t ldw, const void* bias,
                                float* out, int64_t ldo, float* x, int64_t ldx, float alpha, int M, int N,
-                               int K, hipStream_t s);
-// f32 GEMM (small f32 workloads); bias f32; rms_cols handled by rms_heads_f32.
+                               int K, int n_cu, hipStream_t s);
+// f32 GEMM (small f32 workloads); bias f32; the per-head norm of the rms_cols
+// (head_dim 16, 32, 64 or 128) in the epilogue, or by rms_heads_f32 where a head
+// is wider than a tile.
 hipError_t launch_gemm_f32(const GemmArgs* g, int n, int head_dim, int n_cu, hipStream_t s);
 
 // Flash attention, bf16, head_dim 128. vt = v transposed per head:
@@ -94,7 +96,7 @@ hipError_t launch_flash_attn_small_bf16(const void* q, int64_t ldq, const void* 
 // (nullptr) every work-group takes whole query blocks.
 bool flash_attn_uses_ws(int Lq, int Lk, int heads, int nseq, int n_cu);
 size_t flash_attn_ws_bytes(int n_cu);
-// f32 attention, head_dim <= 128 (multiple of 4).
+// f32 attention, head_dim 16, 32, 64 or 128.
 hipError_t launch_attn_f32(const float* q, int64_t ldq, const float* k, int64_t ldk,
                            const float* v, int64_t ldv, float* o, int64_t ldo, int Lq, int Lk,
                            int heads, int head_dim, hipStream_t s);

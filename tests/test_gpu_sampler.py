@@ -86,8 +86,11 @@ def test_small_f32_parity():
     (4, 16, 37, 5, 21, 33, 7),        # odd widths: no 16-byte rows; heads of half a tile
     (1, 64, 256, 16, 64, 15, 2),      # less than one 16-row tile; heads wider than the tile
     (2, 128, 300, 12, 50, 260, 21),   # 128-wide heads
-    (8, 64, 512, 16, 64, 1100, 52),   # 64 x 64 tiles, heads of one tile
-    (32, 16, 500, 16, 64, 1100, 52),  # 64 x 64 tiles, four heads a tile
+    (8, 64, 512, 16, 64, 1100, 52),   # many 32 x 32 tiles, heads wider than those
+    (32, 16, 500, 16, 64, 1100, 52),  # many 32 x 32 tiles, two heads a tile
+    (10, 64, 320, 16, 64, 400, 20),   # 64 x 64 tiles (QKV: 240), heads of one tile
+    (40, 16, 320, 16, 64, 400, 20),   # the same, four heads a tile
+    (4, 32, 512, 16, 64, 64, 16),     # 16 x 16 tiles, the norm's layer on 32 x 32
 ])
 def test_f32_layer_shapes(monkeypatch, heads, hd, F, C, ctx, N, Nt):
     """The f32 GEMM's tile sizes, shared K, unaligned rows and fused norm, and
