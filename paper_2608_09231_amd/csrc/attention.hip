@@ -68,15 +68,15 @@ constexpr int TILE_BYTES = 2 * KT * D * 2;
 // exp(s - 11.5) <= 1.
 constexpr float BOUNDED_SHIFT_LOG2 = 11.5f * 1.4426950408889634f;
 
-// What bounds it: at many keys the board's power (the clock sits near 1.9 GHz)
+// What bounds it: at many keys the board's power (the clock sits near 2.05 GHz)
 // and the softmax beside the products (VALU and MFMA each about 0.6 busy); at
 // 512 keys the queries and outputs on their way from and to HBM; at few items
 // the last, partly filled round of the chip.  Measured in turn on one card
 // through the entry point (transpose included) against one work-group per item
 // on 32x32x16 MFMAs: 32760 x 32760, 40 heads 18.1 -> 17.4 ms; 16896^2, 24 heads
 // (6.2 rounds) 3200 -> 2752 us; 4352^2, 48 heads (3.2 rounds) 517 -> 436 us;
-// 4608^2, 24 heads (1.7 rounds) 265 -> 255 us; 1536^2, 96 heads 170 -> 148 us;
-// 32760 x 512, 40 heads 491 -> 419 us; 5000^2, 3 heads 133 -> 72 us.
+// 4608^2, 24 heads (1.7 rounds) 275 -> 260 us; 1536^2, 96 heads 170 -> 148 us;
+// 32760 x 512, 40 heads 483 -> 410 us; 5000^2, 3 heads 133 -> 72 us.
 //
 // One launch runs at most one work-group per CU (all of LDS) over a list of
 // (sequence, head, 256-query block) items; see Plan.  Per key tile t of an

@@ -745,14 +745,13 @@ constexpr int PIECE_WAVE = 64 * 128;  // floats of a wave's part of a piece, in 
 // A was mostly written just before.
 //
 // What bounds it is the board's power: under these launches the clock sits at
-// 1.7-1.9 GHz and falls as the MFMAs get busier, so energy per product counts,
+// 1.9-2.1 GHz (of 2.4) and falls as the MFMAs get busier, so energy per product counts,
 // not issue slots.  16x16x32 MFMAs read and write each accumulator once per
 // 32 of K (32x32x16: once per 16) for the same fragment reads from LDS, and
 // give the same bits.  Measured against 32x32x16 in turn on one card, through
-// the entry point: 4608 x 9216 x 3072 with the RMS norm 247.5 -> 232.0 us,
-// 4608 x 12288 x 3072 GELU 329.6 -> 307.5, 4608 x 3072 x 12288 gated 289.4 ->
-// 274.7, 8192^3 plain 1356 -> 1413 TFLOP/s, 32760 x 13824 x 5120 GELU 3566 ->
-// 3432 us.  With 32x32x16, four waves of 128 x 128 (two thirds of the LDS
+// the entry point: 4608 x 9216 x 3072 with the RMS norm 235.0 -> 223.2 us, 4608 x
+// 12288 x 3072 GELU 327 -> 307, 4608 x 3072 x 12288 gated 295 -> 272, 8192^3 plain
+// 1356 -> 1413 TFLOP/s, 32760 x 13824 x 5120 GELU 3505 -> 3280 us.  With 32x32x16, four waves of 128 x 128 (two thirds of the LDS
 // reads) ran at 0.99 of the eight waves' rate in the main loop and at 0.92-0.96
 // over the K = 3072 layers, whose epilogue then has one wave per SIMD.
 //
@@ -1167,8 +1166,9 @@ struct Cfg {
 // chooser minimises rounds x per-round work / eff over the configs a
 // problem admits.  The 32 x 128 tiles keep three slices in flight and two
 // work-groups per CU, for few rows against many weights: 28 x 52224 x 3072
-// 89.5 -> 72.4 us (32 x 256 tiles, one slice in flight), 512 x 3072 x 4096 60.7 ->
-// 48.2 us; in two rounds they lose (256 x 9216 x 3072: 90 against 71 us).
+// 93 -> 80 us (32 x 256 tiles, one slice in flight), 512 x 3072 x 4096 60.7 -> 45.5
+// us; past 512 of them 512 x 9216 x 3072 76 against 56 us, 256 x 18432 x 3072 94
+// against 79 (but 128 x 18432 x 3072 68 against 84).
 #define DIT_DMA_CFG(BM, BN, WGM, WGN, BK_, ST, WPC, EFF)                                      \
   {BM, BN, BN / WGN, WPC, 64 * WGM * WGN, BK_,                                                 \
    kLdsEpilogue<BN / WGN, WGM * WGN, ST * (BM + BN) * BK_ * 2>, EFF, true,                     \
@@ -1271,8 +1271,9 @@ int pick_cfg(const GemmArgs* g, int n, int n_cu, bool ws) {
   };
   // Few tiles: at most one 32 x 64 (with the norm 32 x 128) tile per CU.  Through
   // the entry point, small kernel against 32 x 128 tiles with four slices in
-  // LDS: 48 tiles, K = 3072 30 / 39 us; 81, K = 1920 25 / 30; 192, K = 256 16 / 18;
-  // the line is crossed between 288 (K = 3072: 54 / 52) and 512 (K = 1024: 26 / 24).
+  // LDS: 48 tiles, K = 3072 30.3 / 30.7 us; 80, K = 1920 24.8 / 25.6; 96, K = 256 16.0 /
+  // 17.9; 256, K = 1024 22.1 / 21.9; past one per CU 288, K = 3072 46 / 31, 384, K = 1024
+  // 25.7 / 21.8.  (K that is no multiple of 64 leaves the register-staged kernel.)
   {
     const int c = kSmallCfg + (rms ? 1 : 0);
     bool one_chain = false;
