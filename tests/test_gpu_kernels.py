@@ -488,3 +488,63 @@ def test_component_bits_do_not_depend_on_calls_in_flight():
         [t.join() for t in ts]
         for o in outs:
             assert torch.equal(o, alone)
+
+
+def strided(torch, bits, ld, fill=0x7fc0):
+    """Rows of `bits` in a wider buffer whose other columns hold NaN."""
+    b = np.full((bits.shape[0], ld), fill, np.uint16)
+    b[:, :bits.shape[1]] = bits
+    return dev(torch, b)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (33, 392, 40), (70, 520, 200), (28, 1160, 3072),   # small kernel: K off its steps, ragged tiles, whole K shared out
+    (100, 17000, 448),                                 # 32 x 128 tiles
+    (600, 1928, 1024), (4300, 4104, 2112),             # 128 x 128 tiles; ring, shared last round
+])
+@pytest.mark.parametrize("norm", [False, True])
+def test_gemm_strided_forms(M, N, K, norm):
+    """Row strides wider than the rows on every operand, a column gap, GELU
+    from a column inside a tile and the norm on the first heads: the output's
+    columns, and none beside them, in every kernel that takes such a call."""
+    torch = torch_cuda()
+    a_b, a = make((M, K))
+    w_b, w = make((N, K), 0.05)
+    b_b, b = make((N,), 0.1)
+    gelu_from, gap, ldc = 260, 12, N + 12 + 4
+    out = torch.full((M, ldc), 0x7fc0, dtype=torch.int16, device="cuda")
+    binding.gemm_bf16(strided(torch, a_b, K + 8), strided(torch, w_b, K + 16), dev(torch, b_b), out, M=M, N=N, K=K,
+                      lda=K + 8, ldw=K + 16, ldc=ldc, rms_cols=256 if norm else 0, gelu_from=gelu_from,
+                      gap_at=gelu_from, gap=gap)
+    rows = np.unique(np.concatenate([[0, M - 1], RNG.choice(M, min(M, 80), replace=False)]))
+    y = a[rows] @ w.T + b
+    if norm:
+        y[:, :256] = dit.rms_heads(y[:, :256], 2, 128)
+    y[:, gelu_from:] = dit.gelu_tanh(y[:, gelu_from:])
+    got = host_bf16(out)
+    assert np.all(np.isnan(got[:, gelu_from:gelu_from + gap])) and np.all(np.isnan(got[:, N + gap:]))
+    assert_bf16_close(np.concatenate([got[rows, :gelu_from], got[rows, gelu_from + gap:N + gap]], axis=1), round_bf16(y))
+
+
+@pytest.mark.parametrize("bounded", [True, False])
+@pytest.mark.parametrize("Lq,Lk,heads", [(40, 300, 2), (300, 3000, 2), (9000, 130, 8)])
+def test_attention_strided_forms(Lq, Lk, heads, bounded):
+    """The same for attention (small kernel; list kernel with and without a
+    shared last round), v at an odd stride."""
+    torch = torch_cuda()
+    H = heads * 128
+
+    def mk(n, norm):
+        x = RNG.standard_normal((n, H)) * 2.0
+        b = bf16_bits(dit.rms_heads(x, heads, 128) if norm else x)
+        return b, bits_to_f64(b)
+    (q_b, q), (k_b, k), (v_b, v) = mk(Lq, bounded), mk(Lk, bounded), mk(Lk, False)
+    o = torch.full((Lq, H + 4), 0x7fc0, dtype=torch.int16, device="cuda")
+    ws = torch.zeros(H * ((Lk + 63) // 64 * 64), dtype=torch.int16, device="cuda")
+    binding.attention_bf16(strided(torch, q_b, H + 8), strided(torch, k_b, H + 16), strided(torch, v_b, H + 1), o, Lq=Lq,
+                           Lk=Lk, heads=heads, ldq=H + 8, ldk=H + 16, ldv=H + 1, ldo=H + 4, vt_ws=ws,
+                           flags=binding.ATTN_BOUNDED_LOGITS if bounded else 0)
+    got = host_bf16(o)
+    assert np.all(np.isnan(got[:, H:])) and np.all(np.isfinite(got[:, :H]))
+    rows = np.unique(np.concatenate([[0, Lq - 1], RNG.choice(Lq, min(Lq, 40), replace=False)]))
+    assert rel_l2(got[rows, :H], round_bf16(dit.attention(q[rows], k, v, heads, 128))) < 4e-3
